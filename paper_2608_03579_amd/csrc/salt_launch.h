@@ -177,11 +177,12 @@ inline bool configure_launch(ApplyLaunch& a, int n_cu, int n_groups_c, int64_t s
     // columns); the launch splits them evenly over one round of blocks
     jb.cpb = kChunkCols * CW;
     jb.n_col = cdiv(jb.out, jb.cpb);
-    jb.shrink_base = sb;
-    jb.expand_base = eb;
+    jb.shrink_base = a.shrink_base[j] = sb;
+    jb.expand_base = a.expand_base[j] = eb;
     sb += shrink_tiles(a) * jb.S * a.nq;
     eb += a.n_tiles * jb.n_col;
   }
+  for (int j = a.n_jobs; j < kMaxJobs; ++j) a.shrink_base[j] = a.expand_base[j] = INT32_MAX;
   a.shrink_blocks = sb;
   a.expand_items = eb;
   return true;
