@@ -48,17 +48,19 @@ namespace {
 // the shrink, B_c in the expand); the block then loads it once, cooperatively,
 // into an LDS stage from which each wave reads its MFMA fragments, so the
 // operand is read from L2 once per M tokens.
+//
+// Two lane layouts, row and quad (salt_layout.h); quad_expand says which expands
+// use the latter, and the shrink does for residual ranks above 2.
 template <int M>
 constexpr int waves_along() { return waves_of(M) / (M / 16); }
 template <int M>
 constexpr int threads_of() { return 64 * waves_of(M); }
 // Waves per SIMD the kernels for 128-token tiles are compiled for (two blocks
 // of 8 waves per compute unit) where their registers fit that without
-// spilling: r_c <= 32 with residual ranks up to 2, r_c <= 64 with rank 1.
-// Other kernels keep the compiler's choice.
+// spilling; other kernels keep the compiler's choice.
 template <typename E, int M, int NB, int RU>
-constexpr int min_waves() {
-  return (sizeof(E) == 2 && M == 128 && ((NB <= 2 && RU <= 2) || (NB <= 4 && RU <= 1))) ? 4 : 1;
+constexpr int expand_waves() {
+  return sizeof(E) == 2 && M == 128 && RU <= 2 && NB <= 4 ? (RU == 1 || NB == 0 ? 4 : 2) : 1;
 }
 template <typename E, int M, int NB>
 constexpr bool staged() { return sizeof(E) == 2 && M > 16 && NB > 0; }
@@ -69,6 +71,10 @@ template <int M>
 constexpr int stage_row_a() { return kStepK * waves_along<M>() + 8; }
 template <int NB>
 constexpr int stage_row_b() { return 16 * NB + 8; }
+// 16-byte units of half an expand stage in the quad layout (four of a chunk's
+// eight column tiles, CW chunks).
+template <int M, int NB>
+constexpr int quad_half() { return waves_along<M>() * 4 * (NB / 2) * 64; }
 template <int NB, int RU>
 constexpr int shrink_wc() { return 16 * NB + RU; }
 // Block-steps (shrink) or block-chunks (expand) per batch: the loads of one
@@ -79,9 +85,63 @@ template <typename E, int M, int NB, int RU>
 constexpr int depth() { return 1; }
 
 
+// The four token records a lane loads rows for: tokens 4 q + j, j = 0..3, of
+// token block mb (quad layout).
+__device__ __forceinline__ void quad_tokens(const ApplyLaunch& a, const TileHdr& th, int mb, int lane, TokRec (&tr)[4]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int k = mb * 16 + quad_row(lane, j);
+    tr[j] = clamp_tok(a, a.srt[tile_pos(th, k)], k < th.n);
+  }
+}
+// Sum over the 16 lanes that share a quad row set: lanes differing in bits 0, 1
+// (the quad) and 4, 5 (the lane groups).
+__device__ __forceinline__ float row_sum(float v) {
+  v += quad_swap<kXor1>(v);
+  v += quad_swap<kXor2>(v);
+  v += __shfl_xor(v, 16);
+  v += __shfl_xor(v, 32);
+  return v;
+}
+
 // ---------------------------------------------------------------------------
 // shrink
 // ---------------------------------------------------------------------------
+// The tile's partial sums of one K range from the KW waves' sums s_red [KW][M][WC]:
+// centroid columns [0, r_c) (rank chunk 0 only; zero without a centroid term),
+// residual columns r_c + r0 + [0, nres).  The whole block calls it, behind a
+// barrier.
+template <int M, int NB, int RU>
+__device__ __forceinline__ void shrink_store(const ApplyLaunch& a, const Job& jb, const ShrinkCoord& sc,
+                                             const TileHdr& th, const float* s_red, bool has_c) {
+  constexpr int KW = waves_along<M>(), NW = waves_of(M), WC = shrink_wc<NB, RU>();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r0 = sc.q * kRankChunk;
+  const int ncent = sc.q == 0 ? a.r_c : 0;
+  const int nres = imax(0, imin(RU, a.r_u - r0));
+  const int ncols = ncent + nres;
+  const Rsrc rp = make_rsrc(a.partials + jb.poff, (uint32_t)((int64_t)jb.S * a.T * a.R * 4));
+  for (int k = wave; k < th.n; k += NW) {
+    for (int cc = lane; cc < ncols; cc += 64) {
+      float v = 0.f;
+      int col;
+      if (cc < ncent) {
+        col = cc;
+        if (has_c) {
+#pragma unroll
+          for (int w = 0; w < KW; ++w) v += s_red[((size_t)w * M + k) * WC + cc];
+        }
+      } else {
+        const int j = cc - ncent;
+        col = a.r_c + r0 + j;
+#pragma unroll
+        for (int w = 0; w < KW; ++w) v += s_red[((size_t)w * M + k) * WC + 16 * NB + j];
+      }
+      buf_store_f32(rp, (uint32_t)(part_off(a, jb, sc.s, th.i0 + k, col) - jb.poff) * 4u, v);
+    }
+  }
+}
+
 // Wave w takes token block mb = w % TB and the kStepK-wide steps kq, kq + KW, ...
 // (kq = w / TB) of the block's K range: block-step j covers steps j KW .. j KW +
 // KW - 1, one per K quarter.  A lane holds token (lane & 15) of its block and,
@@ -98,8 +158,9 @@ constexpr int depth() { return 1; }
 // written into the other half of the LDS stage, so every wait is for loads that
 // were issued a whole block-step earlier.
 template <typename E, int M, int NB, int RU>
-__global__ void __launch_bounds__(threads_of<M>()) __attribute__((amdgpu_waves_per_eu(min_waves<E, M, NB, RU>(), 8)))
+__global__ void __launch_bounds__(threads_of<M>())
 k_shrink(const ApplyLaunch a) {
+  static_assert(RU <= 2, "larger residual ranks run k_shrink_wide");
   using O = Ops<E>;
   using Vec = typename O::Vec;
   constexpr int ES = sizeof(E);
@@ -111,7 +172,6 @@ k_shrink(const ApplyLaunch a) {
   constexpr int PIECES = 16 * NB * 8 * KW;                   // 16-byte pieces of a block-step's A_c slice
   constexpr int NCV = kStage ? (PIECES + NT - 1) / NT : 1;   // staged A_c vectors per thread and block-step
   constexpr int NAC = kStage ? 1 : 2 * NBL;                  // per-lane A_c vectors per step (unstaged)
-  constexpr int RUP = RU <= 2 ? RU : 0;                      // residual ranks in the pipelined operands
   constexpr int U = depth<E, M, NB, RU>();
   extern __shared__ __attribute__((aligned(16))) char lds[];
   float* s_red = reinterpret_cast<float*>(lds);              // [KW][M][WC], after the K loop
@@ -126,8 +186,7 @@ k_shrink(const ApplyLaunch a) {
   const int mb = wave % TB, kq = wave / TB, row = lane & 15, g = lane >> 4;
   const int kt = mb * 16 + row;                              // this lane's token within the tile
   const TokRec tr = clamp_tok(a, a.srt[tile_pos(th, kt)], kt < th.n);
-  const int r0 = sc.q * kRankChunk;                          // first residual rank of this block
-  const bool has_c = NB > 0 && th.c >= 0 && sc.q == 0;
+  const bool has_c = NB > 0 && th.c >= 0;
   const int klo = k_lo(jb, sc.s), khi = k_hi(jb, sc.s), nst = k_steps(jb, sc.s);
   const int nbs = cdiv(nst, KW);                             // block-steps
   const int klast = imax(0, in - 8);                         // last whole vector of a row
@@ -136,12 +195,11 @@ k_shrink(const ApplyLaunch a) {
   const Rsrc rac = make_rsrc(has_c ? static_cast<const char*>(jb.at_c) + (int64_t)th.c * a.r_c * in * ES : nullptr,
                              has_c ? (uint32_t)((int64_t)a.r_c * in * ES) : 0u);
   const uint32_t xrow = tr.tok ? (uint32_t)tr.t * (uint32_t)(in * ES) : kOob;
-  // residual rows r0 + jj of this lane's slot (the zero page where there is none)
-  const char* au[RUP > 0 ? RUP : 1];
+  // residual rows of this lane's slot (the zero page where there is none)
+  const char* au[RU];
 #pragma unroll
-  for (int jj = 0; jj < RUP; ++jj)
-    au[jj] = (tr.res && r0 + jj < tr.r) ? a.pool + atu_byte(a, jb, tr.u, tr.r, r0 + jj, 0) : a.zeros;
-  const char* au_wide = tr.res ? a.pool + atu_byte(a, jb, tr.u, tr.r, r0, 0) : a.zeros;
+  for (int jj = 0; jj < RU; ++jj)
+    au[jj] = (tr.res && jj < tr.r) ? a.pool + atu_byte(a, jb, tr.u, tr.r, jj, 0) : a.zeros;
 
   f32x4 acc[NBL];
 #pragma unroll
@@ -153,7 +211,7 @@ k_shrink(const ApplyLaunch a) {
   // the per-lane operands of a batch: block-steps j0 .. j0 + U - 1
   struct Ops1 {
     Vec x[U][2];
-    Vec u[U][RUP > 0 ? RUP : 1][2];
+    Vec u[U][RU][2];
     Vec ac[U][NAC];
   };
   // first k of this lane's vectors in block-step j (a step past the K range
@@ -170,7 +228,7 @@ k_shrink(const ApplyLaunch a) {
         B.x[u][h] = O::bload(rx, oob_unless(step_ok && k + 8 <= khi, xrow + (uint32_t)(k * ES)));
       }
 #pragma unroll
-      for (int jj = 0; jj < RUP; ++jj)
+      for (int jj = 0; jj < RU; ++jj)
 #pragma unroll
         for (int h = 0; h < 2; ++h)
           B.u[u][jj][h] = O::load(reinterpret_cast<const E*>(au[jj] + imin(kb + kPiece * h, klast) * ES));
@@ -232,46 +290,18 @@ k_shrink(const ApplyLaunch a) {
             }
         }
       }
-      if constexpr (RU <= 2) {
 #pragma unroll
-        for (int jj = 0; jj < RU; ++jj)
+      for (int jj = 0; jj < RU; ++jj)
 #pragma unroll
-          for (int h = 0; h < 2; ++h) accu[jj] = O::dot(B.x[u][h], B.u[u][jj][h], accu[jj]);
-      }
+        for (int h = 0; h < 2; ++h) accu[jj] = O::dot(B.x[u][h], B.u[u][jj][h], accu[jj]);
     }
   };
-  // wide residual ranks: the step's rows of 8 ranks at a time, read in place
-  // (U is 1 for wide ranks)
-  auto compute_wide = [&](const Ops1& B, int j) {
-    if constexpr (RU > 2) {
-      static_assert(U == 1, "wide residual ranks run one block-step per batch");
-      const int kb = lane_k(j);
-      const int64_t rs = (int64_t)in * ES;
-#pragma unroll
-      for (int j8 = 0; j8 < RU; j8 += 8) {
-        Vec uv[8][2];
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-          const char* base = (tr.res && r0 + j8 + jj < tr.r) ? au_wide + (j8 + jj) * rs : a.zeros;
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-            uv[jj][h] = O::load(reinterpret_cast<const E*>(base + imin(kb + kPiece * h, klast) * ES));
-        }
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj)
-#pragma unroll
-          for (int h = 0; h < 2; ++h) accu[j8 + jj] = O::dot(B.x[0][h], uv[jj][h], accu[j8 + jj]);
-      }
-    }
-  };
-
   Ops1 A;
   if constexpr (ES == 4) {
     // fp32: one set of operands, loaded then used (its vectors are twice as wide)
     for (int j = 0; j < nbs; ++j) {
       load(A, j);
       compute(A, 0);
-      compute_wide(A, j);
     }
   } else {
     Ops1 Bb;
@@ -285,14 +315,12 @@ k_shrink(const ApplyLaunch a) {
       write_stage(1);
       load_stage(j + 2 * U);
       compute(A, 0);
-      compute_wide(A, j);
       if constexpr (kStage) __syncthreads();
       if (j + U >= nbs) break;                               // (block-uniform)
       load(A, j + 2 * U);
       write_stage(0);
       load_stage(j + 3 * U);
       compute(Bb, 1);
-      compute_wide(Bb, j + U);
       if constexpr (kStage) __syncthreads();
     }
   }
@@ -319,31 +347,153 @@ k_shrink(const ApplyLaunch a) {
     for (int j = 0; j < RU; ++j) P[kt * WC + 16 * NB + j] = accu[j];
   }
   __syncthreads();
-  // the tile's partial: centroid columns [0, r_c) (chunk 0 only; zero without a
-  // centroid term), residual columns r_c + r0 + [0, nres)
-  const int ncent = sc.q == 0 ? a.r_c : 0;
-  const int nres = imax(0, imin(RU, a.r_u - r0));
-  const int ncols = ncent + nres;
-  const Rsrc rp = make_rsrc(a.partials + jb.poff, (uint32_t)((int64_t)jb.S * a.T * a.R * 4));
-  for (int k = wave; k < th.n; k += NW) {
-    for (int cc = lane; cc < ncols; cc += 64) {
-      float v = 0.f;
-      int col;
-      if (cc < ncent) {
-        col = cc;
-        if (has_c) {
+  shrink_store<M, NB, RU>(a, jb, sc, th, s_red, has_c);
+}
+
+// Residual ranks above 2 (plain LoRA adapters, long-tail concatenated ones): the
+// shrink of a 16-token tile whose tokens bring up to kRankChunk rows of A_u each
+// in this block's rank chunk.  Bound by the bandwidth of those rows (every row is
+// one user's, read once per tile), so the kernel is laid out for rows in flight:
+//  - the tile header carries its group's largest rank: a block of a chunk past
+//    it leaves at once, and a tile of ranks up to G reads one group of rows per
+//    step instead of the chunk's sixteen ranks;
+//  - the centroid part and the residual part run one after the other, and the
+//    residual part in passes of kPass ranks, so that their operands never share
+//    the registers; rows are read in groups of G, the next group's loads in
+//    flight while one computes.
+// Four waves, one per K quarter, layouts as in k_shrink.
+template <typename E, int NB>
+__global__ void __launch_bounds__(threads_of<16>())
+k_shrink_wide(const ApplyLaunch a) {
+  using O = Ops<E>;
+  using Vec = typename O::Vec;
+  constexpr int ES = sizeof(E), M = 16, KW = waves_along<M>(), RU = kRankChunk, WC = shrink_wc<NB, RU>();
+  constexpr int NBL = NB > 0 ? NB : 1;
+  constexpr int G = ES == 4 ? 1 : 2;                         // rows of one group
+  constexpr int kPass = 8;                                   // ranks of one pass over the K range
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  float* s_red = reinterpret_cast<float*>(lds);              // [KW][M][WC]
+
+  const Job& jb = a.jobs[job_of_shrink(a, blockIdx.x)];
+  const ShrinkCoord sc = shrink_coord(a, jb, blockIdx.x);
+  const TileHdr th = shrink_tile(a, sc.tau);
+  const int r0 = sc.q * kRankChunk;                          // first residual rank of this block
+  if (th.n <= 0 || (sc.q > 0 && r0 >= th.r)) return;         // (block-uniform)
+  const int in = jb.in;
+  const int tid = threadIdx.x, lane = tid & 63, kq = tid >> 6, row = lane & 15, g = lane >> 4;
+  TokRec tr[4];
+  quad_tokens(a, th, 0, lane, tr);
+  const bool has_c = NB > 0 && th.c >= 0 && sc.q == 0;
+  const int klo = k_lo(jb, sc.s), khi = k_hi(jb, sc.s);
+  const int step0 = klo / kQuadStep, step1 = cdiv(khi, kQuadStep);
+  const int nbs = cdiv(step1 - step0, KW);                   // block-steps
+  const int klast = imax(0, in - 8);                         // last whole vector of a row
+  float* P = s_red + (size_t)kq * M * WC;
+
+  const Rsrc rx = make_rsrc(jb.x, (uint32_t)((int64_t)a.T * in * ES));
+  uint32_t xrow[4];
 #pragma unroll
-          for (int w = 0; w < KW; ++w) v += s_red[((size_t)w * M + k) * WC + cc];
-        }
-      } else {
-        const int j = cc - ncent;
-        col = a.r_c + r0 + j;
+  for (int j = 0; j < 4; ++j) xrow[j] = tr[j].tok ? (uint32_t)tr[j].t * (uint32_t)(in * ES) : kOob;
+  auto lane_k = [&](int bs) { return klo + (bs * KW + kq) * kQuadStep + quad_elem(lane); };
+  auto load_x = [&](Vec (&x)[4], int bs) {
+    const int k = lane_k(bs);
 #pragma unroll
-        for (int w = 0; w < KW; ++w) v += s_red[((size_t)w * M + k) * WC + 16 * NB + j];
+    for (int j = 0; j < 4; ++j) x[j] = O::bload(rx, oob_unless(k + 8 <= khi, xrow[j] + (uint32_t)(k * ES)));
+  };
+
+  if constexpr (NB > 0) {
+    if (has_c) {
+      const Rsrc rac = make_rsrc(static_cast<const char*>(jb.at_c) + (int64_t)th.c * a.r_c * in * ES,
+                                 (uint32_t)((int64_t)a.r_c * in * ES));
+      f32x4 acc[NBL];
+#pragma unroll
+      for (int nb = 0; nb < NBL; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      Vec x[4];
+      for (int bs = 0; bs < nbs; ++bs) {
+        load_x(x, bs);
+        to_operand<E>(x);
+        const int k0 = klo + (bs * KW + kq) * kQuadStep + 32 * g;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const int k = k0 + 8 * s, r = 16 * nb + row;
+            acc[nb] = O::mma(x[s], O::bload(rac, oob_unless(r < a.r_c && k + 8 <= khi, (uint32_t)((r * in + k) * ES))),
+                             acc[nb]);
+          }
       }
-      buf_store_f32(rp, (uint32_t)(part_off(a, jb, sc.s, th.i0 + k, col) - jb.poff) * 4u, v);
+      // MFMA output: lane holds rank column 16 nb + row of tokens 4 g + e
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) P[(4 * g + e) * WC + 16 * nb + row] = acc[nb][e];
     }
   }
+
+  const char* au[4];
+  int last[4];                                               // each token's last row in the chunk
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    au[j] = tr[j].res ? a.pool + atu_byte(a, jb, tr[j].u, tr[j].r, r0, 0) : a.zeros;
+    last[j] = tr[j].res ? iclamp(tr[j].r - 1 - r0, 0, RU - 1) : 0;
+  }
+  // rows rho .. rho + G - 1 of the chunk in block-step bs; past its own rows a
+  // token's lanes read its last one again (a cache hit, and no second pointer to
+  // keep): the expand never reads the sums of those ranks
+  auto load_rows = [&](Vec (&b)[G][4], int bs, int rho) {
+    const int k = imin(lane_k(bs), klast);
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        b[i][j] = O::load(reinterpret_cast<const E*>(au[j] + (size_t)(uint32_t)((imin(rho + i, last[j]) * in + k) * ES)));
+  };
+  const int nr = th.r - r0;                                  // rows any token of the tile has in the chunk
+  for (int p = 0; p < RU; p += kPass) {
+    if (p >= nr) break;                                      // (block-uniform)
+    float accu[kPass][4];
+#pragma unroll
+    for (int i = 0; i < kPass; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) accu[i][j] = 0.f;
+    auto dots = [&](const Vec (&x)[4], const Vec (&b)[G][4], int i0) {
+#pragma unroll
+      for (int i = 0; i < G; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) accu[i0 + i][j] = O::dot(x[j], b[i][j], accu[i0 + i][j]);
+    };
+    Vec x[4], u0[G][4], u1[G][4];
+    load_x(x, 0);
+    load_rows(u0, 0, p);
+    if (nr - p > G) {
+      for (int bs = 0; bs < nbs; ++bs) {
+#pragma unroll
+        for (int i = 0; i < kPass; i += 2 * G) {
+          load_rows(u1, bs, p + i + G);
+          dots(x, u0, i);
+          if (i + 2 * G < kPass) load_rows(u0, bs, p + i + 2 * G);
+          else load_rows(u0, bs + 1, p);
+          dots(x, u1, i + G);
+        }
+        load_x(x, bs + 1);
+      }
+    } else {
+      for (int bs = 0; bs < nbs; ++bs) {
+        dots(x, u0, 0);
+        load_x(x, bs + 1);
+        load_rows(u0, bs + 1, p);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kPass; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float v = row_sum(accu[i][j]);
+        if (g == 0 && (lane & 3) == j) P[quad_row(lane, j) * WC + 16 * NB + p + i] = v;
+      }
+  }
+  __syncthreads();
+  shrink_store<M, NB, RU>(a, jb, sc, th, s_red, has_c);
 }
 
 // ---------------------------------------------------------------------------
@@ -374,7 +524,6 @@ __device__ __forceinline__ void expand_segment(const ApplyLaunch& a, const Expan
   constexpr int NT = threads_of<M>();
   constexpr int NCV = kStage ? (128 * CW * NB + NT - 1) / NT : 1;   // staged B_c vectors per thread and block-chunk
   constexpr int NBC = kStage ? 1 : 4 * KSL;                  // per-lane B_c vectors per chunk (unstaged)
-  constexpr int RUP = RU <= 2 ? RU : 0;                      // residual ranks in the pipelined operands
   constexpr int U = depth<E, M, NB, RU>();
   float* s_v = reinterpret_cast<float*>(lds);                // [M][R] v of the tile
 
@@ -393,26 +542,21 @@ __device__ __forceinline__ void expand_segment(const ApplyLaunch& a, const Expan
   const int nch = cdiv(chi - clo, kChunkCols);               // 64-column chunks
   const int nbj = cdiv(nch, CW);                             // block-chunks
   const int olast = imax(0, out - 8);
-  // residual ranks past the first chunk (long-tail adapters) are read from s_v
-  // inside the column loop, so the stage then sits after it; otherwise s_v is
-  // dead once v is in registers and the stage takes its place
-  const bool long_tail = RU == kRankChunk && a.r_u > RU;
-  E* s_b = reinterpret_cast<E*>(lds + (long_tail ? sizeof(float) * (size_t)M * R : 0));   // [2][U][64 CW][SRB]
+  E* s_b = reinterpret_cast<E*>(lds);                        // [2][U][64 CW][SRB], once v is in registers
 
   const Rsrc ry = make_rsrc(jb.y, (uint32_t)((int64_t)a.T * out * ES));
   const Rsrc rb = make_rsrc(has_c ? static_cast<const char*>(jb.bt_c) + (int64_t)th.c * out * a.r_c * ES : nullptr,
                             has_c ? (uint32_t)((int64_t)out * a.r_c * ES) : 0u);
   const uint32_t yrow = tr.tok ? (uint32_t)tr.t * (uint32_t)(out * ES) : kOob;
-  const char* bu[RUP > 0 ? RUP : 1];
+  const char* bu[RU];
 #pragma unroll
-  for (int jj = 0; jj < RUP; ++jj)
+  for (int jj = 0; jj < RU; ++jj)
     bu[jj] = (tr.res && jj < tr.r) ? a.pool + bu_byte(a, jb, tr.u, tr.r, jj, 0) : a.zeros;
-  const char* bu_wide = tr.res ? a.pool + bu_byte(a, jb, tr.u, tr.r, 0, 0) : a.zeros;
 
   // the per-lane operands of a batch: block-chunks j0 .. j0 + U - 1
   struct Ops1 {
     Vec y[U][2];
-    Vec u[U][RUP > 0 ? RUP : 1][2];
+    Vec u[U][RU][2];
     Vec bc[U][NBC];
   };
   // this lane's first column in block-chunk j
@@ -428,7 +572,7 @@ __device__ __forceinline__ void expand_segment(const ApplyLaunch& a, const Expan
 #pragma unroll
       for (int h = 0; h < 2; ++h) B.y[u][h] = O::bload(ry, y_off(j, h));
 #pragma unroll
-      for (int jj = 0; jj < RUP; ++jj)
+      for (int jj = 0; jj < RU; ++jj)
 #pragma unroll
         for (int h = 0; h < 2; ++h)
           B.u[u][jj][h] = O::load(reinterpret_cast<const E*>(bu[jj] + imin(cl + kPiece * h, olast) * ES));
@@ -587,7 +731,6 @@ __device__ __forceinline__ void expand_segment(const ApplyLaunch& a, const Expan
   }
 
   auto compute1 = [&](const Ops1& B, int half, int u, int j) {
-    const int cl = lane_col(j);
     f32x4 d[4];
 #pragma unroll
     for (int b4 = 0; b4 < 4; ++b4) d[b4] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -615,68 +758,15 @@ __device__ __forceinline__ void expand_segment(const ApplyLaunch& a, const Expan
     for (int b4 = 0; b4 < 4; ++b4)
 #pragma unroll
       for (int e = 0; e < 4; ++e) yf[4 * b4 + e] += d[b4][e];
-    if constexpr (RU <= 2) {
 #pragma unroll
-      for (int jj = 0; jj < RU; ++jj)
+    for (int jj = 0; jj < RU; ++jj)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          float b[8];
-          O::to_f32(B.u[u][jj][h], b);
+      for (int h = 0; h < 2; ++h) {
+        float b[8];
+        O::to_f32(B.u[u][jj][h], b);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) yf[8 * h + e] = fmaf(vu[jj], b[e], yf[8 * h + e]);
-        }
-    } else {
-      // wide residual ranks: this chunk's columns of 8 ranks at a time, read in place
-      const int64_t rs = (int64_t)out * ES;
-#pragma unroll
-      for (int j8 = 0; j8 < RU; j8 += 8) {
-        Vec bv[8][2];
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj) {
-          const char* base = (tr.res && j8 + jj < tr.r) ? bu_wide + (j8 + jj) * rs : a.zeros;
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-            bv[jj][h] = O::load(reinterpret_cast<const E*>(base + imin(cl + kPiece * h, olast) * ES));
-        }
-#pragma unroll
-        for (int jj = 0; jj < 8; ++jj)
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            float b[8];
-            O::to_f32(bv[jj][h], b);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) yf[8 * h + e] = fmaf(vu[j8 + jj], b[e], yf[8 * h + e]);
-          }
+        for (int e = 0; e < 8; ++e) yf[8 * h + e] = fmaf(vu[jj], b[e], yf[8 * h + e]);
       }
-      if (long_tail) {
-        // ranks past the first chunk (their v from s_v), eight rows at a time up
-        // to the batch's largest rank, so that eight rows' loads are in flight
-        // together; a lane past its own rank reads the zero page with a zero v
-        for (int r8 = RU; r8 < a.r_u; r8 += 8) {
-          Vec bv[8][2];
-          float vr[8];
-#pragma unroll
-          for (int jj = 0; jj < 8; ++jj) {
-            const int rho = r8 + jj;
-            const bool ok = tr.res && rho < tr.r;
-            const char* base = ok ? bu_wide + rho * rs : a.zeros;
-            vr[jj] = ok ? vrow[a.r_c + rho] : 0.f;
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-              bv[jj][h] = O::load(reinterpret_cast<const E*>(base + imin(cl + kPiece * h, olast) * ES));
-          }
-#pragma unroll
-          for (int jj = 0; jj < 8; ++jj)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              float b[8];
-              O::to_f32(bv[jj][h], b);
-#pragma unroll
-              for (int e = 0; e < 8; ++e) yf[8 * h + e] = fmaf(vr[jj], b[e], yf[8 * h + e]);
-            }
-        }
-      }
-    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) O::bstore(ry, y_off(j, h), yf + 8 * h);
   };
@@ -709,19 +799,377 @@ __device__ __forceinline__ void expand_segment(const ApplyLaunch& a, const Expan
   }
 }
 
+// Wave w takes token block mb = w % TB and, in block-chunk j, the 128-column chunk
+// j CW + cq (cq = w / TB) of the block's columns.  A chunk's y and each residual
+// rank's B_u row pieces are four loads in the quad layout (salt_layout.h), and y
+// is stored the same way.  The centroid part is eight 16 x 16 MFMA tiles
+// D[col][token] = Bt_c[col][:] . v_c[token][:], whose rows are ordered
+// (quad_col) so that a lane's tiles 2 s and 2 s + 1 are the eight columns 32 g +
+// 8 s + 0..7 of token lane & 15; a transpose inside the quads brings them to the
+// layout of y, where y, centroid part and residual part (fp32 FMAs) are added and
+// rounded once.
+// y and B_c go through buffer resources (masked lanes load zeros at kOob, and
+// their stores are dropped), the residual rows through per-lane pointers; the
+// loads are pipelined one block-chunk ahead as in the shrink.
+template <typename E, int M, int NB, int RU>
+__device__ __forceinline__ void expand_segment_quad(const ApplyLaunch& a, const ExpandSeg& sg, char* lds) {
+  using O = Ops<E>;
+  using Vec = typename O::Vec;
+  constexpr int ES = sizeof(E);
+  constexpr bool kBf16 = ES == 2;
+  constexpr int TB = M / 16, CW = waves_along<M>(), KS = NB / 2;
+  constexpr bool kStage = staged<E, M, NB>();
+  constexpr bool kRoll = !kStage && kBf16 && NB > 0 && NB <= 4;   // B_c fragments loaded a chunk ahead
+  constexpr int KSL = KS > 0 ? KS : 1;
+  constexpr int NT = threads_of<M>();
+  constexpr int HALF = quad_half<M, NB>();             // units of one stage half
+  constexpr int NCV = kStage ? (HALF + NT - 1) / NT : 1;     // of them, per thread
+  constexpr bool kWide = RU > 2;                             // residual rows read group by group
+  constexpr int RUP = kWide ? 1 : RU;                        // residual ranks in the pipelined operands
+  constexpr int G = ES == 4 ? 1 : 2;                         // rows of one group (kWide)
+  float* s_v = reinterpret_cast<float*>(lds);                // [M][R] v of the tile
+
+  const Job& jb = a.jobs[sg.job];
+  const TileHdr th = expand_tile(a, sg.tau);
+  if (th.n <= 0) return;                                     // (no tile is empty)
+  const int out = jb.out;
+  // (through an identity permutation, so that what follows from it is worked out
+  // per segment: kept in registers over the walk of the segments, the lane's
+  // addresses spill)
+  const int tid = RU == 1 && M == 128 ? (int)quad_swap<kSelf>((uint32_t)threadIdx.x) : (int)threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int R = a.R;
+  const int mb = wave % TB, cq = wave / TB, row = lane & 15, g = lane >> 4;
+  TokRec tr[4];
+  quad_tokens(a, th, mb, lane, tr);
+  const bool has_c = NB > 0 && th.c >= 0;
+  // the segment's columns: block-chunks [j0, j1) of the tile
+  const int clo = imin(out, sg.j0 * jb.cpb), chi = imin(out, sg.j1 * jb.cpb);
+  const int nbj = cdiv(cdiv(chi - clo, kQuadCols), CW);      // block-chunks
+  const int olast = imax(0, out - 8);
+  // residual ranks above 2 read their v from s_v inside the column loop, so the
+  // stage then sits after it; otherwise s_v is dead once v is in registers and
+  // the stage takes its place
+  E* s_b = reinterpret_cast<E*>(lds + (kWide ? sizeof(float) * (size_t)M * R : 0));   // [2][CW][4][KS][64] units
+
+  const Rsrc ry = make_rsrc(jb.y, (uint32_t)((int64_t)a.T * out * ES));
+  const Rsrc rb = make_rsrc(has_c ? static_cast<const char*>(jb.bt_c) + (int64_t)th.c * out * a.r_c * ES : nullptr,
+                            has_c ? (uint32_t)((int64_t)out * a.r_c * ES) : 0u);
+  uint32_t yrow[4];
+  const char* bu[4][RUP];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    yrow[j] = tr[j].tok ? (uint32_t)tr[j].t * (uint32_t)(out * ES) : kOob;
+#pragma unroll
+    for (int jj = 0; jj < RUP; ++jj)
+      bu[j][jj] = (tr[j].res && jj < tr[j].r) ? a.pool + bu_byte(a, jb, tr[j].u, tr[j].r, jj, 0) : a.zeros;
+  }
+
+  struct Set {
+    Vec y[4];
+    Vec u[4][RUP];
+  };
+  // this lane's first column in block-chunk j
+  auto lane_col = [&](int j) { return clo + (j * CW + cq) * kQuadCols + quad_elem(lane); };
+  auto y_off = [&](int col, int j) { return oob_unless(col + 8 <= chi, yrow[j] + (uint32_t)(col * ES)); };
+  auto load = [&](Set& B, int bj) {
+    const int col = lane_col(bj);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) B.y[j] = O::bload(ry, y_off(col, j));
+    if constexpr (!kWide) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int jj = 0; jj < RUP; ++jj)
+          B.u[j][jj] = O::load(reinterpret_cast<const E*>(bu[j][jj] + imin(col, olast) * ES));
+    }
+  };
+  // fragment ks of column tile t in block-chunk bj
+  auto load_frag = [&](int bj, int t, int ks) {
+    const int o = clo + (bj * CW + cq) * kQuadCols + quad_col(row, t), rk = 32 * ks + 8 * g;
+    return O::bload(rb, oob_unless(o < chi && rk < a.r_c, (uint32_t)((o * a.r_c + rk) * ES)));
+  };
+  Vec bc[kRoll ? 8 : 1][KSL];
+  // Half h of block-chunk bj's B_c slice: the columns of tiles 4 h .. 4 h + 3 (16 of
+  // every 32), all r_c ranks of each, runs of 16 columns contiguous in global
+  // memory; thread piece q holds 8 ranks of one column, st_off[q] elements from
+  // the slice's first, and goes to unit st_slot[q] (fixed for the block).  In the stage a fragment is 64 units of 16
+  // bytes in lane order, but for an exchange inside each row of 16 by rank group,
+  // without which a column's rank groups would share their LDS banks.
+  Vec stg[NCV];
+  int st_off[NCV], st_slot[NCV];
+  auto slot = [&](int cw, int t4, int ks, int gg, int i) {
+    return ((cw * 4 + t4) * KSL + ks) * 64 + 16 * gg + (i ^ (gg + 4 * (ks & 1)));
+  };
+  if constexpr (kStage) {
+    const int rc8 = imax(a.r_c / 8, 1);
+#pragma unroll
+    for (int q = 0; q < NCV; ++q) {
+      const int e = q * NT + tid, c = e / rc8, r8 = e - c * rc8;
+      const int oc = 128 * (c >> 6) + 32 * ((c >> 4) & 3) + (c & 15);
+      st_off[q] = c < 64 * CW ? oc * a.r_c + 8 * r8 : (1 << 30);
+      st_slot[q] = slot(oc >> 7, (oc >> 2) & 3, r8 >> 2, r8 & 3, 4 * ((oc >> 5) & 3) + (oc & 3));
+    }
+  }
+  auto load_stage = [&](int bj, int h) {
+    if constexpr (kStage) {
+      const int c0 = clo + bj * kQuadCols * CW + 16 * h;
+#pragma unroll
+      for (int q = 0; q < NCV; ++q)
+        stg[q] = O::bload(rb, oob_unless(st_off[q] < (chi - c0) * a.r_c, (uint32_t)(c0 * a.r_c + st_off[q]) * (uint32_t)ES));
+    }
+  };
+  auto write_stage = [&](int h) {
+    if constexpr (kStage) {
+#pragma unroll
+      for (int q = 0; q < NCV; ++q)
+        if (st_off[q] < (1 << 30)) *reinterpret_cast<Vec*>(s_b + 8 * (h * HALF + st_slot[q])) = stg[q];
+    }
+  };
+
+  // first loads (they need no v), then v of the tile: the K ranges' partials
+  // summed in order
+  Set A;
+  load_stage(0, 0);
+  load(A, 0);
+  if constexpr (kRoll) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) bc[t][ks] = load_frag(0, t, ks);
+  }
+  {
+    // the tile's rows of one K range are contiguous: (n R / 4) float4 from row
+    // i0; per pass, thread t sums float4 q0 + t and q0 + t + NT over the
+    // K ranges in order, with four K ranges' loads in flight at a time (rows
+    // past n read zero)
+    const Rsrc rp = make_rsrc(a.partials + jb.poff, (uint32_t)((int64_t)jb.S * a.T * a.R * 4));
+    const uint32_t sstride = (uint32_t)a.T * (uint32_t)R * 4u;
+    const uint32_t tile0 = (uint32_t)th.i0 * (uint32_t)R * 4u;
+    // float4 columns [c0, c0 + w4) of the R / 4: with wide ranks only those that
+    // the tile's tokens use (no centroid: none of its columns; ranks up to the
+    // tile's bound), which are also the only ones its shrink blocks wrote
+    const int c0 = kWide && !has_c ? a.r_c / 4 : 0;
+    const int w4 = kWide ? cdiv(a.r_c + imax(th.r, 1), 4) - c0 : R / 4;
+    const int n4 = th.n * w4, m4 = M * w4;
+    constexpr int QMAX = M == 128 ? 1 : 2;                   // float4 per thread and pass
+    for (int q0 = tid; q0 < m4; q0 += QMAX * NT) {
+      float4 v[QMAX];
+      uint32_t off[QMAX];
+#pragma unroll
+      for (int i = 0; i < QMAX; ++i) {
+        const int q = q0 + i * NT;
+        const int p4 = kWide ? q / w4 * (R / 4) + c0 + q % w4 : q;   // place in the tile's rows
+        v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        off[i] = oob_unless(q < n4, tile0 + 16u * (uint32_t)p4);
+      }
+      int sl = 0;
+      for (; sl + 4 <= jb.S; sl += 4) {
+        float4 p[4][QMAX];
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+          for (int i = 0; i < QMAX; ++i) p[d][i] = buf_load_f32x4(rp, off[i] + (uint32_t)(sl + d) * sstride);
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+#pragma unroll
+          for (int i = 0; i < QMAX; ++i) v[i] = f4_add(v[i], p[d][i]);
+      }
+      for (; sl < jb.S; ++sl) {
+        float4 p[QMAX];
+#pragma unroll
+        for (int i = 0; i < QMAX; ++i) p[i] = buf_load_f32x4(rp, off[i] + (uint32_t)sl * sstride);
+#pragma unroll
+        for (int i = 0; i < QMAX; ++i) v[i] = f4_add(v[i], p[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < QMAX; ++i) {
+        const int q = q0 + i * NT;
+        const int p4 = kWide ? q / w4 * (R / 4) + c0 + q % w4 : q;
+        if (q < m4) reinterpret_cast<float4*>(s_v)[p4] = v[i];
+      }
+    }
+  }
+  __syncthreads();
+
+  // centroid v as the MFMA's right operand: column = token lane & 15, k = ranks
+  // 32 ks + 8 g .. + 7, scaled by gamma; ranks past r_c are zero
+  const int b = lane & 3;                                    // (that token is the lane's load j = b)
+  const bool own_tok = b < 2 ? (b == 0 ? tr[0].tok : tr[1].tok) : (b == 2 ? tr[2].tok : tr[3].tok);
+  const float gam = __uint_as_float(b < 2 ? (b == 0 ? tr[0].gamma_bits : tr[1].gamma_bits)
+                                          : (b == 2 ? tr[2].gamma_bits : tr[3].gamma_bits));
+  Vec vhi[KSL], vlo[KSL];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    const float* vrow = s_v + (mb * 16 + row) * R + 32 * ks + 8 * g;
+    // (r_c is a multiple of 8: a group of 8 ranks is wholly inside or past it)
+    float4 va = make_float4(0.f, 0.f, 0.f, 0.f), vb = va;
+    if (own_tok && has_c && 32 * ks + 8 * g < a.r_c) {
+      va = reinterpret_cast<const float4*>(vrow)[0];
+      vb = reinterpret_cast<const float4*>(vrow)[1];
+    }
+    float f[8] = {va.x * gam, va.y * gam, va.z * gam, va.w * gam, vb.x * gam, vb.y * gam, vb.z * gam, vb.w * gam};
+    if constexpr (kBf16) {
+      uint32_t h[8], l[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        h[e] = f32_to_bf16_rne(f[e]);
+        l[e] = f32_to_bf16_rne(f[e] - __uint_as_float(h[e] << 16));
+      }
+      vhi[ks] = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+      vlo[ks] = make_uint4(l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16));
+    } else {
+      vhi[ks].lo = make_float4(f[0], f[1], f[2], f[3]);
+      vhi[ks].hi = make_float4(f[4], f[5], f[6], f[7]);
+      vlo[ks] = O::zero();
+    }
+  }
+  // residual v of the lane's four tokens
+  float vu[4][RUP];
+  if constexpr (!kWide) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int jj = 0; jj < RUP; ++jj)
+        vu[j][jj] = (tr[j].res && jj < tr[j].r) ? s_v[(mb * 16 + quad_row(lane, j)) * R + a.r_c + jj] : 0.f;
+  }
+  if constexpr (kStage) {
+    __syncthreads();
+    // the fragments' rank padding [r_c, 16 NB) reads as zero
+    const int pad = 2 * NB - a.r_c / 8;
+    for (int i = tid; i < 2 * CW * 64 * pad; i += NT) {
+      const int r8 = a.r_c / 8 + i % pad, c = i / pad;       // c: 64 columns of a half, CW chunks, both halves
+      *reinterpret_cast<Vec*>(s_b + 8 * (c / (64 * CW) * HALF + slot(c / 64 % CW, (c >> 2) & 3, r8 >> 2, r8 & 3,
+                                                                     4 * ((c >> 4) & 3) + (c & 3)))) = O::zero();
+    }
+    write_stage(0);
+    load_stage(0, 1);
+    __syncthreads();
+  }
+
+  // wide residual ranks: rows rho .. rho + G - 1 of the lane's tokens at its
+  // columns from col (the zero page past a token's own rank), and their share of y
+  auto load_rows = [&](Vec (&w)[G][4], int rho, int col) {
+    const int c = imin(col, olast);
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const char* base = tr[j].res && rho + i < tr[j].r ? bu[j][0] + (size_t)(uint32_t)((rho + i) * out * ES) : a.zeros;
+        w[i][j] = O::load(reinterpret_cast<const E*>(base + c * ES));
+      }
+  };
+  auto add_rows = [&](const Vec (&w)[G][4], int rho, float (&yf)[4][8]) {
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float v = tr[j].res && rho + i < tr[j].r ? s_v[(mb * 16 + quad_row(lane, j)) * R + a.r_c + rho + i] : 0.f;
+        float f[8];
+        O::to_f32(w[i][j], f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) yf[j][e] = fmaf(v, f[e], yf[j][e]);
+      }
+  };
+  auto mma_half = [&](f32x4 (&d)[8], int bj, int h) {
+    // (a tile without a centroid multiplies zeros: no branch in the loop)
+#pragma unroll
+    for (int t4 = 0; t4 < 4; ++t4)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int t = 4 * h + t4;
+        Vec bf;
+        if constexpr (kStage)
+          bf = *reinterpret_cast<const Vec*>(s_b + 8 * (h * HALF + slot(cq, t4, ks, g, row)));
+        else if constexpr (kRoll)
+          bf = bc[t][ks];
+        else
+          bf = load_frag(bj, t, ks);
+        d[t] = O::mma(bf, vhi[ks], d[t]);
+        if constexpr (kBf16) d[t] = O::mma(bf, vlo[ks], d[t]);
+        if constexpr (kRoll) bc[t][ks] = load_frag(bj + 1, t, ks);
+      }
+  };
+  for (int bj = 0; bj < nbj; ++bj) {
+    const int col = lane_col(bj);
+    Vec w0[kWide ? G : 1][4], w1[kWide ? G : 1][4];
+    if constexpr (kWide) load_rows(w0, 0, col);
+    write_stage(1);
+    load_stage(bj + 1, 0);
+    f32x4 d[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) d[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    mma_half(d, bj, 0);
+    if constexpr (kStage) __syncthreads();
+    write_stage(0);
+    load_stage(bj + 1, 1);
+    mma_half(d, bj, 1);
+    if constexpr (kStage) __syncthreads();
+    uint32_t w[4][8];
+    if constexpr (NB > 0) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[t >> 1][4 * (t & 1) + e] = __float_as_uint(d[t][e]);
+      quad_transpose(w);
+    }
+    if constexpr (!kWide) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float yf[8];
+        O::to_f32(A.y[j], yf);
+        if constexpr (NB > 0) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) yf[e] += __uint_as_float(w[j][e]);
+        }
+#pragma unroll
+        for (int jj = 0; jj < RUP; ++jj) {
+          float f[8];
+          O::to_f32(A.u[j][jj], f);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) yf[e] = fmaf(vu[j][jj], f[e], yf[e]);
+        }
+        O::bstore(ry, y_off(col, j), yf);
+      }
+    } else {
+      float yf[4][8];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        O::to_f32(A.y[j], yf[j]);
+        if constexpr (NB > 0) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) yf[j][e] += __uint_as_float(w[j][e]);
+        }
+      }
+      // groups of G rows up to the tile's bound, the next group's loads in flight
+      for (int r = 0; r < th.r; r += 2 * G) {
+        load_rows(w1, r + G, col);
+        add_rows(w0, r, yf);
+        if (r + G >= th.r) break;                            // (block-uniform)
+        load_rows(w0, r + 2 * G, col);
+        add_rows(w1, r + G, yf);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) O::bstore(ry, y_off(col, j), yf[j]);
+    }
+    if (bj + 1 < nbj) load(A, bj + 1);
+  }
+}
+
 // One round of blocks; block b walks its contiguous share of the launch's work
 // items segment by segment (a segment: the block-chunks of one tile).  Every
 // segment starts behind a block barrier, so its LDS writes never meet the
 // previous segment's reads.
 template <typename E, int M, int NB, int RU>
-__global__ void __launch_bounds__(threads_of<M>()) __attribute__((amdgpu_waves_per_eu(min_waves<E, M, NB, RU>(), 8)))
+__global__ void __launch_bounds__(threads_of<M>()) __attribute__((amdgpu_waves_per_eu(expand_waves<E, M, NB, RU>(), 8)))
 k_expand(const ApplyLaunch a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int end = expand_begin(a, blockIdx.x + 1, gridDim.x);
   for (int pos = expand_begin(a, blockIdx.x, gridDim.x); pos < end;) {
     const ExpandSeg sg = expand_seg(a, pos, end);
     __syncthreads();
-    expand_segment<E, M, NB, RU>(a, sg, lds);
+    if constexpr (quad_expand(M, RU)) expand_segment_quad<E, M, NB, RU>(a, sg, lds);
+    else expand_segment<E, M, NB, RU>(a, sg, lds);
     pos += sg.j1 - sg.j0;                                    // (>= 1)
   }
 }
@@ -737,18 +1185,24 @@ void launch_k(K kernel, int blocks, int threads, size_t lds, hipStream_t s, cons
 }
 
 template <typename E, int M, int NB, int RU>
+auto shrink_kernel() {
+  if constexpr (RU > 2) return k_shrink_wide<E, NB>;
+  else return k_shrink<E, M, NB, RU>;
+}
+template <typename E, int M, int NB, int RU>
 size_t shrink_lds() {
   const size_t red = sizeof(float) * (size_t)waves_along<M>() * M * shrink_wc<NB, RU>();
   const size_t stg = staged<E, M, NB>() ? sizeof(E) * 2 * depth<E, M, NB, RU>() * 16 * NB * stage_row_a<M>() : 0;
   return red > stg ? red : stg;
 }
 template <typename E, int M, int NB, int RU>
-size_t expand_lds(int R, int r_u) {
-  const size_t stg =
-      staged<E, M, NB>() ? sizeof(E) * 2 * depth<E, M, NB, RU>() * 64 * waves_along<M>() * stage_row_b<NB>() : 0;
+size_t expand_lds(int R) {
+  const size_t half = quad_expand(M, RU) ? (size_t)16 * quad_half<M, NB>()
+                                         : sizeof(E) * depth<E, M, NB, RU>() * 64 * waves_along<M>() * stage_row_b<NB>();
+  const size_t stg = staged<E, M, NB>() ? 2 * half : 0;
   const size_t sv = sizeof(float) * (size_t)M * R;
-  // the stage takes the place of v unless long-tail ranks read v in the column loop
-  return (RU == kRankChunk && r_u > RU) ? sv + stg : std::max(sv, stg);
+  // the stage takes the place of v unless wide ranks read v in the column loop
+  return RU > 2 ? sv + stg : std::max(sv, stg);
 }
 
 // Blocks of `kernel` with `lds` bytes of LDS that one compute unit holds at once
@@ -772,14 +1226,21 @@ int resident_blocks(K kernel, int threads, size_t lds) {
 template <typename E, int M, int NB, int RU>
 hipError_t launch_mnr(const ApplyLaunch& a, hipStream_t s, hipEvent_t* ev) {
   constexpr int NT = threads_of<M>();
-  constexpr int MS = M > 64 ? 64 : M;                         // tokens per shrink tile
+  constexpr int MS = RU > 2 ? 16 : (M > 64 ? 64 : M);         // tokens per shrink tile (shrink_tile_tokens)
   if (a.MS != MS) return hipErrorInvalidValue;
-  launch_k(k_shrink<E, MS, NB, RU>, a.shrink_blocks, threads_of<MS>(), shrink_lds<E, MS, NB, RU>(), s, a,
+  launch_k(shrink_kernel<E, MS, NB, RU>(), a.shrink_blocks, threads_of<MS>(), shrink_lds<E, MS, NB, RU>(), s, a,
            ev ? ev[0] : nullptr, ev ? ev[1] : nullptr);
-  const size_t lds = expand_lds<E, M, NB, RU>(a.R, a.r_u);
+  const size_t lds = expand_lds<E, M, NB, RU>(a.R);
   const int round = resident_blocks(k_expand<E, M, NB, RU>, NT, lds) * std::max(1, a.n_cu);
-  launch_k(k_expand<E, M, NB, RU>, std::min(a.expand_items, round), NT, lds, s, a, ev ? ev[2] : nullptr,
-           ev ? ev[3] : nullptr);
+  // One round of blocks walks the items, an equal share each.  Where some tiles
+  // hold ranks of several chunks an item costs as much as its tokens' ranks, and
+  // equal shares would leave most of the device idle behind the blocks that got
+  // the long ones (Zipf T = 512 with rank-65/66 users: 268 us): eight rounds,
+  // handed out as blocks finish (175 us).  Batches of one chunk (rank-16 LoRA)
+  // keep the one round: 64 us against 70 us.
+  const int rounds = RU > 2 && a.n_pairs > a.n_stiles ? 8 : 1;
+  const int grid = (int)std::min<int64_t>(a.expand_items, (int64_t)rounds * round);
+  launch_k(k_expand<E, M, NB, RU>, grid, NT, lds, s, a, ev ? ev[2] : nullptr, ev ? ev[3] : nullptr);
   return hipGetLastError();
 }
 
@@ -806,11 +1267,14 @@ int shrink_round_m(const ApplyLaunch& a) {
   const int nb = centroid_blocks(a.r_c);
   const int ru = a.r_u <= 1 ? 1 : (a.r_u <= 2 ? 2 : kRankChunk);
 #define SALT_ROUND(NB_, RU_) \
-  if (nb == NB_ && ru == RU_) return round(k_shrink<E, MS, NB_, RU_>, shrink_lds<E, MS, NB_, RU_>());
-  SALT_ROUND(0, 1) SALT_ROUND(0, 2) SALT_ROUND(0, kRankChunk)
-  SALT_ROUND(2, 1) SALT_ROUND(2, 2) SALT_ROUND(2, kRankChunk)
-  SALT_ROUND(4, 1) SALT_ROUND(4, 2) SALT_ROUND(4, kRankChunk)
-  SALT_ROUND(8, 1) SALT_ROUND(8, 2) SALT_ROUND(8, kRankChunk)
+  if (nb == NB_ && ru == RU_) return round(shrink_kernel<E, MS, NB_, RU_>(), shrink_lds<E, MS, NB_, RU_>());
+  SALT_ROUND(0, 1) SALT_ROUND(0, 2)
+  SALT_ROUND(2, 1) SALT_ROUND(2, 2)
+  SALT_ROUND(4, 1) SALT_ROUND(4, 2)
+  SALT_ROUND(8, 1) SALT_ROUND(8, 2)
+  if constexpr (MS == 16) {
+    SALT_ROUND(0, kRankChunk) SALT_ROUND(2, kRankChunk) SALT_ROUND(4, kRankChunk) SALT_ROUND(8, kRankChunk)
+  }
 #undef SALT_ROUND
   return 0;
 }
@@ -871,15 +1335,15 @@ hipError_t kernels_init(int device) {
   hipError_t e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, device);
   if (e != hipSuccess) return e;
   const int R = padded_rank(kMaxRc, kMaxRu);
-  const size_t need_expand = std::max({expand_lds<uint16_t, 64, 8, kRankChunk>(R, kMaxRu),
-                                       expand_lds<uint16_t, 32, 8, kRankChunk>(R, kMaxRu),
-                                       expand_lds<uint16_t, 128, 8, kRankChunk>(R, kMaxRu),
-                                       expand_lds<uint16_t, 128, 4, 2>(padded_rank(64, 2), 2),
-                                       expand_lds<uint16_t, 64, 4, 2>(padded_rank(64, 2), 2),
-                                       expand_lds<uint16_t, 32, 4, 2>(padded_rank(64, 2), 2)});
-  const size_t need_shrink = std::max({shrink_lds<uint16_t, 128, 8, kRankChunk>(),
-                                       shrink_lds<uint16_t, 64, 8, kRankChunk>(), shrink_lds<uint16_t, 32, 8, kRankChunk>(),
-                                       shrink_lds<uint16_t, 64, 4, 2>(), shrink_lds<uint16_t, 32, 4, 2>()});
+  const size_t need_expand = std::max({expand_lds<uint16_t, 64, 8, kRankChunk>(R),
+                                       expand_lds<uint16_t, 32, 8, kRankChunk>(R),
+                                       expand_lds<uint16_t, 128, 8, kRankChunk>(R),
+                                       expand_lds<uint16_t, 128, 4, 2>(padded_rank(64, 2)),
+                                       expand_lds<uint16_t, 64, 4, 2>(padded_rank(64, 2)),
+                                       expand_lds<uint16_t, 32, 4, 2>(padded_rank(64, 2))});
+  const size_t need_shrink = std::max({shrink_lds<uint16_t, 16, 8, kRankChunk>(), shrink_lds<uint16_t, 64, 8, 2>(),
+                                       shrink_lds<uint16_t, 32, 8, 2>(), shrink_lds<uint16_t, 64, 4, 2>(),
+                                       shrink_lds<uint16_t, 32, 4, 2>()});
   const size_t need_plan = (sizeof(uint64_t) + sizeof(int) + 1) * kSortChunk + 256;
   const size_t need = std::max(need_expand, std::max(need_shrink, need_plan));
   if ((size_t)lds_max < need) return hipErrorInvalidConfiguration;

@@ -63,6 +63,36 @@ __device__ __forceinline__ float4 f4_add(float4 a, float4 b) {
 // `off` if `ok`, else the out-of-range offset
 __device__ __forceinline__ uint32_t oob_unless(bool ok, uint32_t off) { return ok ? off : kOob; }
 
+// ---- quads ------------------------------------------------------------------------
+// The value of the lane whose number differs in bit 0 (kXor1) or bit 1 (kXor2).
+constexpr int kXor1 = 0xb1, kXor2 = 0x4e;       // quad permutations [1,0,3,2] and [2,3,0,1]
+constexpr int kSelf = 0xe4;                     // [0,1,2,3]
+template <int P>
+__device__ __forceinline__ uint32_t quad_swap(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, P, 0xf, 0xf, true);
+}
+template <int P>
+__device__ __forceinline__ float quad_swap(float v) { return __uint_as_float(quad_swap<P>(__float_as_uint(v))); }
+// Transposes the 4 registers x 4 lanes of every quad, N words to an entry: lane b,
+// register j receives what lane j held in register b.  All lanes call it.
+template <int N>
+__device__ __forceinline__ void quad_transpose(uint32_t (&w)[4][N]) {
+  const bool b0 = threadIdx.x & 1, b1 = threadIdx.x & 2;
+  auto exchange = [](uint32_t& lo, uint32_t& hi, uint32_t xl, uint32_t xh, bool upper) {
+    lo = upper ? xh : lo;
+    hi = upper ? hi : xl;
+  };
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+#pragma unroll
+    for (int j = 0; j < 4; j += 2)
+      exchange(w[j][n], w[j + 1][n], quad_swap<kXor1>(w[j][n]), quad_swap<kXor1>(w[j + 1][n]), b0);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      exchange(w[j][n], w[j + 2][n], quad_swap<kXor2>(w[j][n]), quad_swap<kXor2>(w[j + 2][n]), b1);
+  }
+}
+
 template <typename E>
 struct Ops;
 
@@ -71,6 +101,9 @@ template <>
 struct Ops<uint16_t> {
   using Vec = uint4;
   static __device__ __forceinline__ Vec zero() { return make_uint4(0u, 0u, 0u, 0u); }
+  static constexpr int kWords = 4;
+  static __device__ __forceinline__ void words(const Vec& v, uint32_t (&w)[4]) { w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w; }
+  static __device__ __forceinline__ Vec vec(const uint32_t (&w)[4]) { return make_uint4(w[0], w[1], w[2], w[3]); }
   static __device__ __forceinline__ Vec load(const uint16_t* p) { return *reinterpret_cast<const uint4*>(p); }
   static __device__ __forceinline__ Vec bload(Rsrc r, uint32_t off) { return buf_load16(r, off); }
   static __device__ __forceinline__ void bstore(Rsrc r, uint32_t off, const float* f) {
@@ -115,6 +148,17 @@ struct Ops<float> {
   static __device__ __forceinline__ Vec zero() {
     return Vec{make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
   }
+  static constexpr int kWords = 8;
+  static __device__ __forceinline__ void words(const Vec& v, uint32_t (&w)[8]) {
+    float f[8];
+    to_f32(v, f);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e] = __float_as_uint(f[e]);
+  }
+  static __device__ __forceinline__ Vec vec(const uint32_t (&w)[8]) {
+    return Vec{make_float4(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]), __uint_as_float(w[3])),
+               make_float4(__uint_as_float(w[4]), __uint_as_float(w[5]), __uint_as_float(w[6]), __uint_as_float(w[7]))};
+  }
   static __device__ __forceinline__ Vec load(const float* p) {
     return Vec{*reinterpret_cast<const float4*>(p), *reinterpret_cast<const float4*>(p + 4)};
   }
@@ -157,5 +201,16 @@ struct Ops<float> {
     return c;
   }
 };
+
+// Four loads of a wave in the quad layout -> operand form (salt_layout.h).
+template <typename E>
+__device__ __forceinline__ void to_operand(typename Ops<E>::Vec (&v)[4]) {
+  uint32_t w[4][Ops<E>::kWords];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) Ops<E>::words(v[j], w[j]);
+  quad_transpose(w);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] = Ops<E>::vec(w[j]);
+}
 
 }  // namespace salt

@@ -35,8 +35,11 @@ inline int choose_tile_tokens(int esize, int T, int n_groups, bool centroids) {
 // size, the first n mod k of them one token longer; for larger tiles
 // k - 1 full tiles and the remainder (the expand of 128-token tiles splits
 // its work by column chunks, not by tiles, so their sizes need not match).
-// Tiles are contiguous in sorted order and cover [0, T).
-inline void cut_tiles(const std::vector<int>& per_c, int M, std::vector<int4>& tiles) {
+// Tiles are contiguous in sorted order and cover [0, T).  rank_c (per_c's
+// layout): each group's largest residual rank, which its tiles' headers carry
+// (null: 0).
+inline void cut_tiles(const std::vector<int>& per_c, int M, std::vector<int4>& tiles,
+                      const std::vector<int>* rank_c = nullptr) {
   tiles.clear();
   int start = 0;
   for (size_t g = 0; g < per_c.size(); ++g) {
@@ -50,13 +53,19 @@ inline void cut_tiles(const std::vector<int>& per_c, int M, std::vector<int4>& t
       t.x = p;
       t.y = len;
       t.z = (int)g - 1;
-      t.w = 0;
+      t.w = rank_c ? (*rank_c)[g] : 0;
       tiles.push_back(t);
       p += len;
     }
     start += n;
   }
 }
+
+// Tokens per shrink tile of a batch whose expand runs M-token tiles.  Up to 64;
+// batches with residual ranks above 2 take 16: their time goes to the tokens'
+// own A_u rows, which no larger tile would share, and the smaller tile spreads
+// the few tiles that hold them over more blocks.
+inline int shrink_tile_tokens(int M, int r_u) { return r_u > 2 ? 16 : std::min(M, 64); }
 
 // Split-K partial floats a plan of up to T tokens holds (rows of R floats): two
 // K ranges per token row for a full launch of kMaxJobs tables, or one if that
@@ -91,8 +100,8 @@ inline bool configure_launch(ApplyLaunch& a, int n_cu, int n_groups_c, int64_t s
   // table carry about the same work, sized for ~target blocks; each table's
   // split is capped so that its partials (written, then read) stay within a
   // tenth of its bytes
-  const int gran = kStepK * KW;
-  const double pairs = (double)shrink_tiles(a) * a.nq;
+  const int gran = (a.r_u > 2 ? kQuadStep : kStepK) * KW;
+  const double pairs = a.n_pairs > 0 ? (double)a.n_pairs : (double)shrink_tiles(a) * a.nq;
   const int kc_target = std::max(gran, cdiv((int)std::ceil((double)sum_in * pairs / target), gran) * gran);
   const double part_row = 8.0 * a.T * a.R;        // bytes of one K range's partials, written and read
   std::vector<int> S(a.n_jobs), s_cap(a.n_jobs);
@@ -175,7 +184,7 @@ inline bool configure_launch(ApplyLaunch& a, int n_cu, int n_groups_c, int64_t s
     poff += (int64_t)jb.S * a.T * a.R;
     // expand: work items of one block-chunk (kChunkCols per wave along the
     // columns); the launch splits them evenly over one round of blocks
-    jb.cpb = kChunkCols * CW;
+    jb.cpb = (quad_expand(a.M, a.r_u) ? kQuadCols : kChunkCols) * CW;
     jb.n_col = cdiv(jb.out, jb.cpb);
     jb.shrink_base = a.shrink_base[j] = sb;
     jb.expand_base = a.expand_base[j] = eb;

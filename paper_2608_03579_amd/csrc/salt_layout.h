@@ -30,6 +30,8 @@ namespace salt {
 constexpr int kWaves = 4;            // waves of an apply block for tiles of up to 32 tokens
 constexpr int kStepK = 64;           // k elements one wave takes per shrink step
 constexpr int kChunkCols = 64;       // output columns one wave takes per expand chunk
+constexpr int kQuadStep = 128;       // the same in the quad layout (lane layouts, below)
+constexpr int kQuadCols = 128;
 constexpr int kMaxJobs = 16;         // tables one apply launch serves
 constexpr int kRankChunk = 16;       // residual ranks one shrink block accumulates
 constexpr int kMaxRc = 128;          // largest centroid rank
@@ -57,7 +59,8 @@ SALT_HD int padded_rank(int r_c, int r_u) {
 
 // ---- records ------------------------------------------------------------------
 // A tile is a run of at most M sorted tokens of one centroid group: header
-// (first sorted position i0, token count n, centroid c or -1, 0).  A token
+// (first sorted position i0, token count n, centroid c or -1, largest residual
+// rank of its centroid group).  A token
 // record at sorted position p is (token t, slot u or -1, residual rank r,
 // gamma bits).
 
@@ -99,7 +102,8 @@ struct ApplyLaunch {
   int32_t n_tiles;
   const int4* stiles;      // [n_stiles] the shrink's tiles (the expand's tiles unless those exceed 64 tokens)
   int32_t n_stiles;
-  int32_t MS;              // tokens per shrink tile (min(M, 64))
+  int32_t MS;              // tokens per shrink tile (shrink_tile_tokens)
+  int32_t n_pairs;         // (shrink tile, residual rank chunk) pairs that hold a rank, or 0: n_stiles * nq
   int32_t M;               // tokens per tile (16, 32 or 64)
   int32_t C, r_c;
   int32_t n_slots;
@@ -114,6 +118,7 @@ struct ApplyLaunch {
 
 struct TileHdr {
   int i0, n, c;
+  int r;                   // bound of the residual ranks of the tile's tokens
 };
 struct TokRec {
   int t, u, r;
@@ -123,12 +128,13 @@ struct TokRec {
 };
 
 // A tile header with every field clamped: 0 <= i0 < T, 0 <= n <= min(M, T -
-// i0), -1 <= c < C (M: the tile size of the list it comes from).
+// i0), -1 <= c < C, 0 <= r <= r_u (M: the tile size of the list it comes from).
 SALT_HD TileHdr clamp_tile(const ApplyLaunch& a, int4 h, int M) {
   TileHdr r;
   r.i0 = iclamp(h.x, 0, imax(a.T - 1, 0));
   r.n = iclamp(h.y, 0, imin(M, a.T - r.i0));
   r.c = (a.r_c > 0) ? iclamp(h.z, -1, a.C - 1) : -1;
+  r.r = iclamp(h.w, 0, a.r_u);
   return r;
 }
 
@@ -266,5 +272,33 @@ constexpr int kPiece = 32;
 SALT_HD int expand_col(int col0, int i, int b4) {
   return col0 + kPiece * (b4 >> 1) + 8 * (i >> 2) + 4 * (b4 & 1) + (i & 3);
 }
+
+// ---- lane layouts ----------------------------------------------------------------
+// Row layout: a lane holds a token row (lane & 15), as the matrix instructions hold
+// their operands, and of a 64-wide step or chunk the two vectors above.
+// Quad layout: a wave works on 16 token rows x 128 consecutive elements, 16 vectors
+// of eight per row, and loads them so that the four lanes of a quad take four
+// consecutive vectors of one row: lane l = 16 g + 4 q + b reads in load j (0..3)
+// row 4 q + j, vector 4 g + b.  The memory pipeline takes a wave's 16-byte lanes
+// quad by quad, one 64-byte piece each; in the row layout every lane is a piece
+// of its own, and the address units of the prefill's expand were busy 73 % of
+// the time (45 % in the quad layout, 236 -> 212 us).
+// A transpose of 4 registers x 4 lanes inside each quad turns loads j into the
+// operand form: lane l, register s holds row l & 15, vector 4 g + s, that is
+// elements 32 g + 8 s + 0..7.
+SALT_HD int quad_row(int lane, int j) { return 4 * ((lane >> 2) & 3) + j; }
+SALT_HD int quad_elem(int lane) { return 32 * (lane >> 4) + 8 * (lane & 3); }
+// Column of row i of 16-column tile t (0..7) of a 128-column chunk in the quad
+// layout: the product's lane (token, g), which receives rows 4 g + e, e = 0..3,
+// of every tile, holds of tiles 2 s and 2 s + 1 the columns 32 g + 8 s + 0..7.
+SALT_HD int quad_col(int i, int t) { return 32 * (i >> 2) + 4 * t + (i & 3); }
+
+// Whether the expand runs in the quad layout: 128-token tiles and residual ranks
+// above 2, whose time is the streams of rows themselves.  Smaller tiles of ranks
+// up to 2 keep the row layout, whose shorter chunks, two sets of operands and
+// cheaper set-up serve short groups better (Llama-3.1-8B decode T = 256: 34.5 us
+// against 36 us, Zipf T = 512: 35 against 39, 64-token tiles of rank 2: 41
+// against 49).
+SALT_HD constexpr bool quad_expand(int M, int r_u) { return M == 128 || r_u > 2; }
 
 }  // namespace salt

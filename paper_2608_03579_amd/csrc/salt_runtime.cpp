@@ -111,6 +111,7 @@ struct salt_plan {
   int32_t n_tiles = 0;
   int32_t MS = 16;                  // tokens per shrink tile
   int32_t n_stiles = 0;             // shrink tiles: 0 when they are the tiles themselves
+  int32_t n_pairs = 0;              // (shrink tile, residual rank chunk) pairs that hold a rank
   int32_t n_groups_c = 0;           // centroids referenced
   int32_t ru_max = 0;               // largest residual rank referenced
   int64_t sum_rank = 0;             // ranks summed over the distinct referenced slots
@@ -360,6 +361,7 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
   SALT_HIP(ctx, close_readers(ctx, plan));
   std::vector<int32_t> slots;
   std::vector<int> per_c((size_t)C + 1, 0);   // tokens per centroid id (+1 for c = -1)
+  std::vector<int> rank_c((size_t)C + 1, 0);  // and their largest residual rank
   int ru_max = 0;
   for (int t = 0; t < T; ++t) {
     const int u = tok_u[t];
@@ -369,7 +371,9 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
     std::memcpy(&gbits, &g, 4);
     plan->staging[t] = make_int4(tok_c[t], u, r, gbits);
     if (u >= 0) slots.push_back(u);
-    per_c[(size_t)tok_c[t] + 1]++;
+    const size_t grp = (size_t)(tok_c[t] + 1);
+    per_c[grp]++;
+    rank_c[grp] = std::max(rank_c[grp], r);
     ru_max = std::max(ru_max, r);
   }
   std::sort(slots.begin(), slots.end());
@@ -388,12 +392,14 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
       n_groups_c += (g > 0);
     }
   plan->M = salt::choose_tile_tokens((int)ctx->esize, T, n_groups, n_groups_c > 0);
-  // tiles of more than 64 tokens serve the expand only; the shrink then runs
-  // its own 64-token tiles of the same sorted order
+  // where the shrink's tiles differ (shrink_tile_tokens), the expand's tiles
+  // serve the expand only and the shrink runs its own of the same sorted order
   std::vector<int4> tiles, stiles;
-  salt::cut_tiles(per_c, plan->M, tiles);
-  plan->MS = std::min(plan->M, 64);
-  if (plan->MS != plan->M) salt::cut_tiles(per_c, plan->MS, stiles);
+  salt::cut_tiles(per_c, plan->M, tiles, &rank_c);
+  plan->MS = salt::shrink_tile_tokens(plan->M, ru_max);
+  if (plan->MS != plan->M) salt::cut_tiles(per_c, plan->MS, stiles, &rank_c);
+  plan->n_pairs = 0;
+  for (const int4& t : plan->MS != plan->M ? stiles : tiles) plan->n_pairs += std::max(1, salt::cdiv(t.w, salt::kRankChunk));
   if ((int)tiles.size() > plan->tile_cap || (int)stiles.size() > plan->tile_cap)
     return fail(ctx, SALT_ERR_BAD_STATE, "%zu tiles exceed the plan's %d", std::max(tiles.size(), stiles.size()),
                 plan->tile_cap);
@@ -494,6 +500,7 @@ salt_status apply_impl(salt_ctx* ctx, int32_t n, const int32_t* tables, salt_pla
     a.stiles = plan->n_stiles ? plan->staged_dev + T + plan->n_tiles : a.tiles;
     a.n_stiles = plan->n_stiles ? plan->n_stiles : plan->n_tiles;
     a.MS = plan->MS;
+    a.n_pairs = plan->n_pairs;
     a.srt = plan->srt;
     a.pool = ctx->pool;
     a.partials = partials;

@@ -336,6 +336,17 @@ inline T __shfl_down(T v, unsigned d, int = 64) {
   const int l = salt_cpu::lane();
   return salt_cpu::wave_xchg(v, l + (int)d < 64 ? l + (int)d : l);
 }
+// the quad permutations of the DPP controls (lane b of a quad reads lane (ctrl >> 2 b) & 3 of it)
+inline int salt_cpu_update_dpp(int, int v, int ctrl, int, int, bool) {
+  const int l = salt_cpu::lane();
+  if (ctrl < 0 || ctrl > 0xff) {
+    fprintf(stderr, "only quad permutations are modelled (DPP control %#x)\n", ctrl);
+    abort();
+  }
+  return salt_cpu::wave_xchg(v, (l & ~3) | ((ctrl >> (2 * (l & 3))) & 3));
+}
+#define __builtin_amdgcn_update_dpp salt_cpu_update_dpp
+#define __builtin_amdgcn_sched_barrier(mask)   // an order hint for the GPU compiler only
 inline int atomicAdd(int* p, int v) {
   const int o = *p;
   *p = o + v;
