@@ -168,7 +168,7 @@ k_shrink(const ApplyLaunch a) {
   constexpr bool kStage = staged<E, M, NB>();
   constexpr int NBL = NB > 0 ? NB : 1;
   constexpr int SR = stage_row_a<M>();                       // elements per staged A_c row
-  constexpr int NT = threads_of<M>(), NW = waves_of(M);
+  constexpr int NT = threads_of<M>();
   constexpr int PIECES = 16 * NB * 8 * KW;                   // 16-byte pieces of a block-step's A_c slice
   constexpr int NCV = kStage ? (PIECES + NT - 1) / NT : 1;   // staged A_c vectors per thread and block-step
   constexpr int NAC = kStage ? 1 : 2 * NBL;                  // per-lane A_c vectors per step (unstaged)
@@ -532,7 +532,7 @@ __device__ __forceinline__ void expand_segment(const ApplyLaunch& a, const Expan
   if (th.n <= 0) return;                                     // (no tile is empty)
   const int out = jb.out;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int R = a.R, VW = imin(a.r_c + a.r_u, R);
+  const int R = a.R;
   const int mb = wave % TB, cq = wave / TB, row = lane & 15, g = lane >> 4;
   const int kt = mb * 16 + row;                              // this lane's token within the tile
   const TokRec tr = clamp_tok(a, a.srt[tile_pos(th, kt)], kt < th.n);

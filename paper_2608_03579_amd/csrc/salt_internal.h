@@ -43,24 +43,33 @@ struct FuseArgs {
 };
 
 // Gram products of two low-rank updates dW_k = A_k B_k per table (factor form):
-// g holds, per table and factor side (At: over in, B: over out), the Grams
-// X1 X2^T [nb1*16][nb2*16], X1 X1^T [nb1*16][nb1*16], X2 X2^T [nb2*16][nb2*16]
-// (ranks padded to 16); out[3 t + 0..2] = Tr(dW1^T dW2), ||dW1||^2, ||dW2||^2.
-struct GramTable {
-  const void* at1;          // [r1][in]
-  const void* b1;           // [r1][out]
-  const void* at2;          // [r2][in]
-  const void* b2;           // [r2][out]
+// the Grams X1 X2^T [nb1*16][nb2*16], X1 X1^T [nb1*16][nb1*16], X2 X2^T
+// [nb2*16][nb2*16] (ranks padded to 16) of each table's two factor sides (At: over
+// in, B: over out).  For ranks up to 32 g holds them per (table, K chunk), the
+// in chunks first, each written by one block; above, per table and side, summed
+// with atomics in a cleared g.  out[3 t + 0..2] = Tr(dW1^T dW2), ||dW1||^2, ||dW2||^2.
+struct GramTable {          // a context's tables, on the device since salt_create
+  int64_t prefix;           // sum of (in + out) over the earlier tables
   int32_t in_dim, out_dim;
 };
 struct GramArgs {
   const GramTable* tabs;    // [n_tables], device
+  const char* blob1;        // table after table At [r][in], B [r][out]
+  const char* blob2;
   int32_t n_tables, r1, r2;
-  float* g;                 // zeroed by the caller
-  size_t g_table, g_side;   // floats per table, per factor side
+  int32_t kc, chunks;       // K elements of a chunk; chunks a table has at most
+  float* g;
+  size_t g_table, g_side;   // floats per table, per chunk or per factor side
   int32_t g_12, g_11, g_22; // floats of each Gram
-  double* out;              // [n_tables][3], device
+  double* out;              // [n_tables][3], device-visible
 };
+// Whether adapters of ranks r1, r2 take the per-chunk Grams, and their chunk length:
+// per chunk up to rank 32, where a wave holds every tile of a step; 1024 elements
+// split two rank-16 adapters over 196 tables into 1,700 blocks, two rounds of the
+// device.  Above rank 32 per-chunk Grams would grow the scratch with the square
+// of the rank (1.2 GB for rank 256), so those sum with atomics.
+constexpr bool gram_per_chunk(int r1, int r2) { return r1 <= 32 && r2 <= 32; }
+constexpr int gram_chunk(int r1, int r2) { return gram_per_chunk(r1, r2) ? 1024 : 2048; }
 
 // Residual blobs one swap launch gathers from mapped page-locked host memory:
 // blob i is vecs[i] 16-byte vectors from src[i] (a device-visible host address)
@@ -93,9 +102,9 @@ hipError_t launch_apply(const ApplyLaunch& a, hipStream_t s, hipEvent_t* ev);
 int shrink_round_blocks(const ApplyLaunch& a);
 // e0 / e1: if set, HIP events that record the fuse kernel's own start and end.
 hipError_t launch_fuse(const FuseArgs& f, int bf16, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
-// k_gram then k_gram_finish on s; max_in / max_out: largest in / out over the tables.
+// k_gram then k_gram_finish on s (g cleared by the caller unless gram_per_chunk).
 // k_swap_gather on s: every blob of a (n <= kSwapMax) in one launch.
 hipError_t launch_swap(const SwapArgs& a, hipStream_t s);
-hipError_t launch_gram(const GramArgs& a, int max_in, int max_out, int bf16, hipStream_t s);
+hipError_t launch_gram(const GramArgs& a, int bf16, hipStream_t s);
 
 }  // namespace salt

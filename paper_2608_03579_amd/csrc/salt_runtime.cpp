@@ -149,8 +149,11 @@ struct salt_ctx {
   char* pool = nullptr;
   size_t slot_stride = 0;
   char* zeros = nullptr;                 // zero page of max(in, out) * esize bytes, never written after set-up
+  salt::GramTable* gram_tabs = nullptr;  // the tables as salt_adapter_gram's kernels read them, since set-up
   char* gram = nullptr;                  // salt_adapter_gram's device scratch, grown on demand
   size_t gram_bytes = 0;
+  double* gram_out = nullptr;            // its results [n_tables][3], page-locked, written by the device
+  double* gram_out_dev = nullptr;        // the same as the device addresses them
   hipStream_t side = nullptr;
   // bookkeeping
   std::vector<int32_t> slot_rank;        // -1 = never loaded
@@ -294,6 +297,8 @@ void destroy_ctx_memory(salt_ctx* c) {
   if (c->pool) (void)hipFree(c->pool);
   if (c->zeros) (void)hipFree(c->zeros);
   if (c->gram) (void)hipFree(c->gram);
+  if (c->gram_tabs) (void)hipFree(c->gram_tabs);
+  if (c->gram_out) (void)hipHostFree(c->gram_out);
   for (hipEvent_t e : c->readers.ev)
     if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->loaders.ev)
@@ -795,6 +800,21 @@ salt_status salt_create(const salt_config* cfg, salt_ctx** out) {
     (void)hipGetLastError();
     return bail(SALT_ERR_OUT_OF_MEMORY, hipSuccess, "");
   }
+  std::vector<salt::GramTable> gt(c->tables.size());
+  for (size_t t = 0; t < gt.size(); ++t)
+    gt[t] = salt::GramTable{c->tab_prefix[t], c->tables[t].in_dim, c->tables[t].out_dim};
+  if (hipMalloc((void**)&c->gram_tabs, gt.size() * sizeof(salt::GramTable)) != hipSuccess) {
+    (void)hipGetLastError();
+    return bail(SALT_ERR_OUT_OF_MEMORY, hipSuccess, "");
+  }
+  if (hipHostMalloc((void**)&c->gram_out, gt.size() * 3 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return bail(SALT_ERR_OUT_OF_MEMORY, hipSuccess, "");
+  }
+  e = hipHostGetDevicePointer((void**)&c->gram_out_dev, c->gram_out, 0);
+  if (e != hipSuccess) return bail(SALT_ERR_HIP, e, "Gram results");
+  e = hipMemcpy(c->gram_tabs, gt.data(), gt.size() * sizeof(salt::GramTable), hipMemcpyHostToDevice);
+  if (e != hipSuccess) return bail(SALT_ERR_HIP, e, "table records");
   e = hipMemset(c->zeros, 0, zero_bytes);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) return bail(SALT_ERR_HIP, e, "zero page");
@@ -1084,23 +1104,6 @@ salt_status salt_adapter_gram(salt_ctx* ctx, const void* blob1, int32_t r1, cons
   SALT_HIP(ctx, hipSetDevice(ctx->device));
   hipStream_t s = (hipStream_t)stream;
   const int nt = ctx->cfg.n_tables;
-  const size_t es = ctx->esize;
-  std::vector<salt::GramTable> tabs(nt);
-  size_t prefix = 0;
-  int max_in = 0, max_out = 0;
-  for (int t = 0; t < nt; ++t) {
-    const salt_shape sh = ctx->tables[t];
-    salt::GramTable& g = tabs[t];
-    g.at1 = static_cast<const char*>(blob1) + (size_t)r1 * prefix * es;
-    g.b1 = static_cast<const char*>(g.at1) + (size_t)r1 * sh.in_dim * es;
-    g.at2 = static_cast<const char*>(blob2) + (size_t)r2 * prefix * es;
-    g.b2 = static_cast<const char*>(g.at2) + (size_t)r2 * sh.in_dim * es;
-    g.in_dim = sh.in_dim;
-    g.out_dim = sh.out_dim;
-    prefix += (size_t)sh.in_dim + sh.out_dim;
-    max_in = std::max(max_in, sh.in_dim);
-    max_out = std::max(max_out, sh.out_dim);
-  }
   const int p1 = (r1 + 15) / 16 * 16, p2 = (r2 + 15) / 16 * 16;
   salt::GramArgs a{};
   a.n_tables = nt;
@@ -1110,12 +1113,18 @@ salt_status salt_adapter_gram(salt_ctx* ctx, const void* blob1, int32_t r1, cons
   a.g_11 = p1 * p1;
   a.g_22 = p2 * p2;
   a.g_side = (size_t)a.g_12 + a.g_11 + a.g_22;
-  a.g_table = 2 * a.g_side;
-  // one scratch buffer per context: table records, then the Grams, then the
-  // results (each region 256-byte aligned); it grows to the largest call so far
-  auto up = [](size_t n) { return (n + 255) / 256 * 256; };
-  const size_t tabs_bytes = up(sizeof(salt::GramTable) * nt), g_bytes = up(sizeof(float) * a.g_table * nt);
-  const size_t need = tabs_bytes + g_bytes + sizeof(double) * 3 * nt;
+  a.blob1 = static_cast<const char*>(blob1);
+  a.blob2 = static_cast<const char*>(blob2);
+  a.tabs = ctx->gram_tabs;
+  const bool per_chunk = salt::gram_per_chunk(r1, r2);
+  a.kc = salt::gram_chunk(r1, r2);
+  a.chunks = 2;
+  for (const salt_shape& sh : ctx->tables)
+    a.chunks = std::max(a.chunks, salt::cdiv(sh.in_dim, a.kc) + salt::cdiv(sh.out_dim, a.kc));
+  a.g_table = (per_chunk ? (size_t)a.chunks : 2) * a.g_side;
+  // one scratch buffer per context for the Grams, which grows to the largest
+  // call so far, and one page-locked buffer that the device writes the results to
+  const size_t need = sizeof(float) * a.g_table * nt;
   if (need > ctx->gram_bytes) {
     // (the previous buffer is idle: every earlier call synchronised its stream)
     if (ctx->gram) (void)hipFree(ctx->gram);
@@ -1128,15 +1137,12 @@ salt_status salt_adapter_gram(salt_ctx* ctx, const void* blob1, int32_t r1, cons
     }
     ctx->gram_bytes = need;
   }
-  char* tabs_d = ctx->gram;
-  a.tabs = reinterpret_cast<const salt::GramTable*>(tabs_d);
-  a.g = reinterpret_cast<float*>(tabs_d + tabs_bytes);
-  a.out = reinterpret_cast<double*>(tabs_d + tabs_bytes + g_bytes);
-  SALT_HIP(ctx, hipMemcpyAsync(tabs_d, tabs.data(), sizeof(salt::GramTable) * nt, hipMemcpyHostToDevice, s));
-  SALT_HIP(ctx, hipMemsetAsync(a.g, 0, sizeof(float) * a.g_table * nt, s));
-  SALT_HIP(ctx, salt::launch_gram(a, max_in, max_out, ctx->cfg.dtype == SALT_BF16, s));
-  SALT_HIP(ctx, hipMemcpyAsync(out, a.out, sizeof(double) * 3 * nt, hipMemcpyDeviceToHost, s));
+  a.g = reinterpret_cast<float*>(ctx->gram);
+  a.out = ctx->gram_out_dev;
+  if (!per_chunk) SALT_HIP(ctx, hipMemsetAsync(a.g, 0, need, s));
+  SALT_HIP(ctx, salt::launch_gram(a, ctx->cfg.dtype == SALT_BF16, s));
   SALT_HIP(ctx, hipStreamSynchronize(s));
+  std::memcpy(out, ctx->gram_out, sizeof(double) * 3 * nt);
   return SALT_OK;
 }
 
