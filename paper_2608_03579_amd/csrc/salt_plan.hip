@@ -4,10 +4,12 @@
 // unique, so the order, the segments (runs of equal (centroid, slot)) and the
 // groups (runs of equal centroid) are unique and bit-exact.
 //
-//   k_plan_sort:   one block per chunk of kSortChunk tokens sorts its keys
-//                  (bitonic network: in-wave steps on registers, the others in
-//                  LDS).  A batch of one chunk is finished in the
-//                  same block; larger batches write their sorted chunks.
+//   k_plan_small:  up to 64 tokens, one wave: the maps come in the kernel's
+//                  arguments, and a key's place is the number of smaller keys.
+//   k_plan_sort:   one block per chunk of up to kSortChunk tokens sorts its keys
+//                  (runs of 64 on registers, then merges in LDS).  A batch of
+//                  one chunk is finished in the same block; larger batches write
+//                  their sorted chunks.
 //   k_plan_merge:  (more than one chunk) a key's place is its place in its own
 //                  chunk plus, for every other chunk, the number of keys below
 //                  it there (binary search).
@@ -25,7 +27,7 @@ namespace salt {
 namespace {
 
 constexpr int kPlanThreads = 1024;
-constexpr uint64_t kPad = ~0ull;
+constexpr uint64_t kPad = 1ull << 63;   // or-ed with a place: above every key
 constexpr uint64_t kTokMask = (1ull << 21) - 1;
 
 // (c + 1) << 42 | (u + 1) << 21 | t: c + 1 <= 64, u + 1 <= 2^20, t < 2^16.
@@ -92,7 +94,7 @@ __device__ __forceinline__ void block_scan2(int c0, int c1, int& e0, int& e1, in
 // the meta words, and the check of the host's tiles.  One block of NT threads;
 // thread i takes places [i per, (i + 1) per).
 template <int NT>
-__device__ void plan_finish(const PlanLaunch& a, const uint64_t* keys, int* s_w) {
+__device__ void plan_finish(const PlanLaunch& a, const uint64_t* keys, const int4* tiles, int* s_w) {
   const int T = a.T, tid = threadIdx.x;
   const int per = cdiv(T, NT);
   const int p0 = imin(T, tid * per), p1 = imin(T, p0 + per);
@@ -124,12 +126,12 @@ __device__ void plan_finish(const PlanLaunch& a, const uint64_t* keys, int* s_w)
   // (centroid first) holds exactly when its first and last keys carry it
   int bad = 0;
   for (int tau = tid; tau < a.n_tiles; tau += NT) {
-    const int4 h = a.tiles[tau];
+    const int4 h = tiles[tau];
     const int i0 = iclamp(h.x, 0, T - 1), n = iclamp(h.y, 0, T - i0);
     const bool first = tau == 0 || tau == a.n_list0, last = tau == a.n_tiles - 1 || tau == a.n_list0 - 1;
     int start = 0;
     if (!first) {
-      const int4 g = a.tiles[tau - 1];
+      const int4 g = tiles[tau - 1];
       start = g.x + g.y;
     }
     if (n != h.y || i0 != h.x || n <= 0 || i0 != start || (last && i0 + n != T) || key_c(keys[i0]) != h.z ||
@@ -159,91 +161,6 @@ __device__ __forceinline__ uint64_t exchange_in_wave(uint64_t x, int p, int j, i
   return keep_min == (x < y) ? x : y;
 }
 
-// One block of NT threads per chunk of at most NC = NT * KPT keys: NT = 1024
-// for batches of more than 512 tokens (KPT = 4, a chunk of kSortChunk keys),
-// otherwise the smallest of 64, 256 or 512 threads that holds the batch (KPT = 1).
-template <int NT>
-__global__ void __launch_bounds__(NT) k_plan_sort(const PlanLaunch a) {
-  constexpr int KPT = NT == kPlanThreads ? kSortChunk / kPlanThreads : 1;   // keys per thread, at most
-  constexpr int NC = NT * KPT;
-  __shared__ uint64_t s_keys[NC];
-  __shared__ int s_gb[NC];                   // gamma bits and rank of the chunk's tokens,
-  __shared__ uint8_t s_r[NC];                // for the records of a one-chunk batch
-  __shared__ int s_w[64];
-  const int tid = threadIdx.x;
-  const int base = blockIdx.x * NC;
-  const int cnt = imin(NC, a.T - base);
-  if (tid == 0 && blockIdx.x == 0) a.meta[kMetaErr] = 0;
-  // the network spans the smallest power of two >= cnt (padding keys sort last)
-  int n2 = 2;
-  while (n2 < cnt) n2 <<= 1;
-  // Bitonic sort, ascending.  Thread tid holds the places tid + NT e,
-  // e < ne; steps whose partners lie within a wave (distance j < 64) run on
-  // registers through lane shuffles, in the waves that hold places; steps of a
-  // larger distance run in LDS, one pair per thread, with a block barrier after
-  // each.  (All loop bounds and the wave test are uniform over a wave.)
-  const int ne = imax(1, n2 / NT);
-  const bool holds = (tid & ~63) < n2;
-  uint64_t r[KPT];
-#pragma unroll
-  for (int e = 0; e < KPT; ++e) {
-    const int p = tid + NT * e;
-    r[e] = kPad;
-    if (e < ne && p < cnt) {
-      const int4 m = a.maps[base + p];
-      r[e] = plan_key(m.x, m.y, base + p);
-      s_gb[p] = m.w;
-      s_r[p] = (uint8_t)iclamp(m.z, 0, 255);
-    }
-  }
-  for (int k = 2; k <= n2; k <<= 1) {
-    if (k / 2 >= 64) {
-#pragma unroll
-      for (int e = 0; e < KPT; ++e)
-        if (e < ne && tid + NT * e < n2) s_keys[tid + NT * e] = r[e];
-      __syncthreads();
-      for (int j = k >> 1; j >= 64; j >>= 1) {
-        for (int i = tid; i < n2 / 2; i += NT) {
-          const int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1)), hi = lo + j;
-          const uint64_t x = s_keys[lo], y = s_keys[hi];
-          if ((x > y) == ((lo & k) == 0)) {
-            s_keys[lo] = y;
-            s_keys[hi] = x;
-          }
-        }
-        __syncthreads();
-      }
-#pragma unroll
-      for (int e = 0; e < KPT; ++e)
-        if (e < ne && tid + NT * e < n2) r[e] = s_keys[tid + NT * e];
-    }
-    if (holds) {
-      for (int j = imin(k >> 1, 32); j > 0; j >>= 1) {
-#pragma unroll
-        for (int e = 0; e < KPT; ++e)
-          if (e < ne) r[e] = exchange_in_wave(r[e], tid + NT * e, j, k);
-      }
-    }
-  }
-  if (gridDim.x == 1) {
-    // (a thread writes the places it alone read last)
-#pragma unroll
-    for (int e = 0; e < KPT; ++e)
-      if (e < ne && tid + NT * e < n2) s_keys[tid + NT * e] = r[e];
-    __syncthreads();
-    for (int i = tid; i < cnt; i += NT) {
-      const uint64_t k = s_keys[i];
-      const int t = iclamp(key_tok(k), 0, cnt - 1);   // (one chunk: base is 0)
-      write_record(a, i, k, s_r[t], s_gb[t]);
-    }
-    plan_finish<NT>(a, s_keys, s_w);
-  } else {
-#pragma unroll
-    for (int e = 0; e < KPT; ++e)
-      if (e < ne && tid + NT * e < cnt) a.keys[base + tid + NT * e] = r[e];
-  }
-}
-
 // Entries of the ascending run l[0, n) below k.
 __device__ __forceinline__ int count_below(const uint64_t* l, int n, uint64_t k) {
   int lo = 0, hi = n;
@@ -253,6 +170,108 @@ __device__ __forceinline__ int count_below(const uint64_t* l, int n, uint64_t k)
     else hi = mid;
   }
   return lo;
+}
+
+// One block of NT threads per chunk of at most NC = NT * KPT keys, KPT keys to a
+// thread: place tid + NT e.  Each wave sorts runs of 64 keys on its registers;
+// then pairs of runs merge, level by level, a key's place being its place in its
+// run plus the number of keys below it in the other (a binary search in LDS).
+// Bound by latency: one barrier to a level, against one to each of the 36 (T =
+// 1531) steps of a whole bitonic network in LDS, which took 22 us; 17 us
+// here, with the maps read over PCIe (12 us of a copy ahead of it gone as well).
+template <int NT, int KPT>
+__global__ void __launch_bounds__(NT) k_plan_sort(const PlanLaunch a) {
+  constexpr int NC = NT * KPT;
+  __shared__ uint64_t s_keys2[2][NC];
+  __shared__ int s_gb[NC];                   // gamma bits and rank of the chunk's tokens,
+  __shared__ uint8_t s_r[NC];                // for the records of a one-chunk batch
+  __shared__ int s_w[64];
+  const int tid = threadIdx.x;
+  const int base = blockIdx.x * NC;
+  const int cnt = imin(NC, a.T - base);
+  if (tid == 0 && blockIdx.x == 0) a.meta[kMetaErr] = 0;
+  // (the block's own finish reads them behind barriers)
+  if (a.tiles_src)
+    for (int i = tid; i < a.n_tiles; i += NT) a.tiles[i] = a.tiles_src[i];
+  uint64_t r[KPT];
+#pragma unroll
+  for (int e = 0; e < KPT; ++e) {
+    const int p = tid + NT * e;
+    r[e] = kPad | (uint64_t)p;               // (above every key, and unique like them)
+    if (p < cnt) {
+      const int4 m = a.maps[base + p];
+      r[e] = plan_key(m.x, m.y, base + p);
+      s_gb[p] = m.w;
+      s_r[p] = (uint8_t)iclamp(m.z, 0, 255);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < KPT; ++e) {
+    if (NT * e + (tid & ~63) < cnt) {        // (a run that holds keys: wave-uniform)
+      for (int k = 2; k <= 64; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) r[e] = exchange_in_wave(r[e], tid & 63, j, k);
+    }
+    s_keys2[0][tid + NT * e] = r[e];
+  }
+  __syncthreads();
+  int cur = 0;
+  int n2 = 64;                               // the merges span the power of two that holds the keys
+  while (n2 < cnt) n2 <<= 1;
+  for (int L = 64; L < n2; L <<= 1) {
+    const uint64_t* src = s_keys2[cur];
+    uint64_t* dst = s_keys2[cur ^ 1];
+#pragma unroll
+    for (int e = 0; e < KPT; ++e) {
+      const int p = tid + NT * e, pair = p & ~(2 * L - 1);
+      if (p >= n2) continue;                 // (wave-uniform)
+      const uint64_t x = src[p];
+      dst[pair + (p & (L - 1)) + count_below(src + ((p & L) ? pair : pair + L), L, x)] = x;
+    }
+    __syncthreads();
+    cur ^= 1;
+  }
+  uint64_t* const s_keys = s_keys2[cur];
+  if (gridDim.x == 1) {
+    for (int i = tid; i < cnt; i += NT) {
+      const uint64_t k = s_keys[i];
+      const int t = iclamp(key_tok(k), 0, cnt - 1);   // (one chunk: base is 0)
+      write_record(a, i, k, s_r[t], s_gb[t]);
+    }
+    plan_finish<NT>(a, s_keys, a.tiles, s_w);
+  } else {
+    for (int i = tid; i < cnt; i += NT) a.keys[base + i] = s_keys[i];
+  }
+}
+
+// Up to 64 tokens, in one wave: a key's place is the number of keys below it, so
+// there is nothing to sort.  Bound by latency (a launch and two rounds to
+// memory): the
+// kernel takes 4.6 us against 4.9, and the copy that the sort waited for is gone
+// (a decode step of four new tokens, maps to y: 30.9 -> 21.6 us).
+__global__ void __launch_bounds__(64) k_plan_small(const PlanLaunch a, const PlanArgs m) {
+  __shared__ uint64_t s_keys[kArgTokens], s_sorted[kArgTokens];
+  __shared__ int4 s_tiles[kArgEntries];
+  __shared__ int s_w[64];
+  const int tid = threadIdx.x, T = imin(a.T, kArgTokens), nt = imin(a.n_tiles, kArgEntries - T);
+  for (int i = tid; i < nt; i += 64) {
+    const int4 h = m.e[T + i];
+    s_tiles[i] = h;
+    a.tiles[i] = h;
+  }
+  const int4 e = m.e[tid];
+  const uint64_t key = tid < T ? plan_key(e.x, e.y, tid) : kPad;
+  s_keys[tid] = key;
+  if (tid == 0) a.meta[kMetaErr] = 0;
+  __syncthreads();
+  int place = 0;
+#pragma unroll 8
+  for (int j = 0; j < T; ++j) place += s_keys[j] < key;
+  if (tid < T) {
+    s_sorted[place] = key;                     // (keys are unique: place < T)
+    write_record(a, place, key, e.z, e.w);
+  }
+  __syncthreads();
+  plan_finish<64>(a, s_sorted, s_tiles, s_w);
 }
 
 __global__ void __launch_bounds__(256) k_plan_merge(const PlanLaunch a) {
@@ -274,20 +293,28 @@ __global__ void __launch_bounds__(256) k_plan_merge(const PlanLaunch a) {
 
 __global__ void __launch_bounds__(kPlanThreads) k_plan_finish(const PlanLaunch a) {
   __shared__ int s_w[64];
-  plan_finish<kPlanThreads>(a, a.keys_sorted, s_w);
+  plan_finish<kPlanThreads>(a, a.keys_sorted, a.tiles, s_w);
 }
 
 }  // namespace
 
-hipError_t launch_plan(const PlanLaunch& a, hipStream_t s) {
+hipError_t launch_plan(const PlanLaunch& a, const PlanArgs* args, hipStream_t s) {
   if (a.T <= 0) return hipSuccess;
   if (a.T > kMaxTokens) return hipErrorInvalidValue;
-  const int nch = cdiv(a.T, kSortChunk);
-  if (a.T <= 64) hipLaunchKernelGGL(k_plan_sort<64>, dim3(1), dim3(64), 0, s, a);
-  else if (a.T <= 256) hipLaunchKernelGGL(k_plan_sort<256>, dim3(1), dim3(256), 0, s, a);
-  else if (a.T <= 512) hipLaunchKernelGGL(k_plan_sort<512>, dim3(1), dim3(512), 0, s, a);
-  else hipLaunchKernelGGL(k_plan_sort<kPlanThreads>, dim3(nch), dim3(kPlanThreads), 0, s, a);
-  if (nch > 1) {
+  if (args) {
+    if (a.T > kArgTokens || a.T + a.n_tiles > kArgEntries) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_plan_small, dim3(1), dim3(64), 0, s, a, *args);
+  } else if (a.T <= 256) {
+    hipLaunchKernelGGL((k_plan_sort<256, 1>), dim3(1), dim3(256), 0, s, a);
+  } else if (a.T <= 512) {
+    hipLaunchKernelGGL((k_plan_sort<512, 1>), dim3(1), dim3(512), 0, s, a);
+  } else if (a.T <= 2 * kPlanThreads) {
+    hipLaunchKernelGGL((k_plan_sort<kPlanThreads, 2>), dim3(1), dim3(kPlanThreads), 0, s, a);
+  } else {
+    const int chunks = cdiv(a.T, kSortChunk);
+    hipLaunchKernelGGL((k_plan_sort<kPlanThreads, kSortChunk / kPlanThreads>), dim3(chunks), dim3(kPlanThreads), 0, s,
+                       a);
+    if (chunks == 1) return hipGetLastError();
     hipLaunchKernelGGL(k_plan_merge, dim3(cdiv(a.T, 256)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_plan_finish, dim3(1), dim3(kPlanThreads), 0, s, a);
   }

@@ -23,6 +23,7 @@
 namespace {
 
 constexpr int kEvRing = 1024;         // reader / loader event rings
+constexpr int kStageRing = 2;         // staging buffers of a plan: the host stages a batch while the last one's build reads its own
 constexpr size_t kAlign = 256;
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -99,9 +100,18 @@ struct salt_plan {
   int32_t* meta = nullptr;          // [kMetaWords]
   float* partials = nullptr;
   size_t partial_cap = 0;           // floats
-  int4* staging = nullptr;          // pinned host copy of maps + tiles
-  hipEvent_t staged = nullptr;      // recorded after the H2D copy of the staging buffer
-  bool staged_pending = false;
+  // pinned host copies of maps + tiles, a ring of kStageRing buffers; `stage` is
+  // the current batch's.  A buffer is written again only after the event behind
+  // its last device read (the copy, or each build in place).
+  int4* staging = nullptr;
+  int4* staging_dev = nullptr;      // the ring as the device addresses it
+  size_t stage_len = 0;             // int4s of one buffer
+  int stage = 0;
+  hipEvent_t staged[kStageRing] = {};
+  bool staged_pending[kStageRing] = {};
+  bool args_only = false;           // every batch travels in the kernel's arguments: the ring is ordinary memory
+  bool in_place = false;            // the batch's builds read the staging buffer in place
+  bool in_args = false;             // or carry it in the kernel's arguments
   hipEvent_t hop = nullptr;         // orders the plan's work across streams
   int32_t max_T = 0, tile_cap = 0;
   // the batch
@@ -283,8 +293,10 @@ void free_plan(salt_plan* p) {
   void* dev[] = {p->staged_dev, p->keys, p->srt, p->ints, p->meta, p->partials};
   for (void* q : dev)
     if (q) (void)hipFree(q);
-  if (p->staging) (void)hipHostFree(p->staging);
-  if (p->staged) (void)hipEventDestroy(p->staged);
+  if (p->args_only) delete[] p->staging;
+  else if (p->staging) (void)hipHostFree(p->staging);
+  for (hipEvent_t e : p->staged)
+    if (e) (void)hipEventDestroy(e);
   if (p->hop) (void)hipEventDestroy(p->hop);
   delete p;
 }
@@ -297,7 +309,6 @@ void destroy_ctx_memory(salt_ctx* c) {
   if (c->pool) (void)hipFree(c->pool);
   if (c->zeros) (void)hipFree(c->zeros);
   if (c->gram) (void)hipFree(c->gram);
-  if (c->gram_tabs) (void)hipFree(c->gram_tabs);
   if (c->gram_out) (void)hipHostFree(c->gram_out);
   for (hipEvent_t e : c->readers.ev)
     if (e) (void)hipEventDestroy(e);
@@ -315,19 +326,30 @@ salt_status plan_create(salt_ctx* ctx, salt_plan** out) {
   p->tile_cap = salt::max_tiles((int)T, ctx->cfg.n_centroids);
   p->partial_cap = salt::plan_partial_cap(T, R);
   const size_t staged = T + 2 * (size_t)p->tile_cap;
+  p->args_only = T <= (size_t)salt::kArgTokens && staged <= (size_t)salt::kArgEntries;
   bool ok = hipMalloc((void**)&p->staged_dev, staged * sizeof(int4)) == hipSuccess &&
             hipMalloc((void**)&p->keys, 2 * T * sizeof(uint64_t)) == hipSuccess &&
             hipMalloc((void**)&p->srt, T * sizeof(int4)) == hipSuccess &&
             hipMalloc((void**)&p->ints, salt_plan::n_ints(T) * 4) == hipSuccess &&
             hipMalloc((void**)&p->meta, salt::kMetaWords * 4) == hipSuccess &&
             hipMalloc((void**)&p->partials, p->partial_cap * 4) == hipSuccess &&
-            hipHostMalloc((void**)&p->staging, staged * sizeof(int4), hipHostMallocDefault) == hipSuccess;
+            (p->args_only ||
+             hipHostMalloc((void**)&p->staging, kStageRing * staged * sizeof(int4), hipHostMallocDefault) == hipSuccess);
+  if (ok && p->args_only) ok = (p->staging = new (std::nothrow) int4[kStageRing * staged]) != nullptr;
   if (!ok) {
     (void)hipGetLastError();
     free_plan(p);
     return fail(ctx, SALT_ERR_OUT_OF_MEMORY, "plan buffers for %zu tokens do not fit", T);
   }
-  hipError_t e = hipEventCreateWithFlags(&p->staged, hipEventDisableTiming);
+  p->stage_len = staged;
+  hipError_t e = hipSuccess;
+  if (!p->args_only) {
+    void* view = nullptr;
+    e = hipHostGetDevicePointer(&view, p->staging, 0);
+    p->staging_dev = static_cast<int4*>(view);
+  }
+  for (int i = 0; i < kStageRing && e == hipSuccess && !p->args_only; ++i)
+    e = hipEventCreateWithFlags(&p->staged[i], hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&p->hop, hipEventDisableTiming);
   if (e == hipSuccess) e = hipMemset(p->meta, 0, salt::kMetaWords * 4);
   if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -357,11 +379,13 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
       return fail(ctx, SALT_ERR_INVALID_ARG, "tok_gamma[%d] is not finite", t);
   }
   SALT_HIP(ctx, hipSetDevice(ctx->device));
-  // the staging buffer may still feed the previous copy
-  if (plan->staged_pending) {
-    SALT_HIP(ctx, hipEventSynchronize(plan->staged));
-    plan->staged_pending = false;
+  // the next staging buffer may still feed an earlier batch's copy or build
+  const int stage = (plan->stage + 1) % kStageRing;
+  if (plan->staged_pending[stage]) {
+    SALT_HIP(ctx, hipEventSynchronize(plan->staged[stage]));
+    plan->staged_pending[stage] = false;
   }
+  int4* const staging = plan->staging + (size_t)stage * plan->stage_len;
   // the previous batch's applies still read the old slots
   SALT_HIP(ctx, close_readers(ctx, plan));
   std::vector<int32_t> slots;
@@ -374,7 +398,7 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
     const float g = tok_gamma ? tok_gamma[t] : 1.0f;
     int32_t gbits;
     std::memcpy(&gbits, &g, 4);
-    plan->staging[t] = make_int4(tok_c[t], u, r, gbits);
+    staging[t] = make_int4(tok_c[t], u, r, gbits);
     if (u >= 0) slots.push_back(u);
     const size_t grp = (size_t)(tok_c[t] + 1);
     per_c[grp]++;
@@ -408,8 +432,11 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
   if ((int)tiles.size() > plan->tile_cap || (int)stiles.size() > plan->tile_cap)
     return fail(ctx, SALT_ERR_BAD_STATE, "%zu tiles exceed the plan's %d", std::max(tiles.size(), stiles.size()),
                 plan->tile_cap);
-  std::copy(tiles.begin(), tiles.end(), plan->staging + T);
-  std::copy(stiles.begin(), stiles.end(), plan->staging + T + tiles.size());
+  std::copy(tiles.begin(), tiles.end(), staging + T);
+  std::copy(stiles.begin(), stiles.end(), staging + T + tiles.size());
+  plan->stage = stage;
+  plan->in_args = T <= salt::kArgTokens && T + (int)(tiles.size() + stiles.size()) <= salt::kArgEntries;
+  plan->in_place = !plan->in_args && T <= salt::kInPlaceTokens;
   plan->n_tiles = (int32_t)tiles.size();
   plan->n_stiles = (int32_t)stiles.size();
   plan->n_groups_c = n_groups_c;
@@ -417,12 +444,12 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
   plan->sum_rank = sum_rank;
   plan->T = T;
   plan->built = false;
-  if (T > 0) {
+  if (T > 0 && !plan->in_place && !plan->in_args) {
     SALT_HIP(ctx, use_stream(ctx, plan, s));
-    SALT_HIP(ctx, hipMemcpyAsync(plan->staged_dev, plan->staging,
+    SALT_HIP(ctx, hipMemcpyAsync(plan->staged_dev, staging,
                                  ((size_t)T + tiles.size() + stiles.size()) * sizeof(int4), hipMemcpyHostToDevice, s));
-    SALT_HIP(ctx, hipEventRecord(plan->staged, s));
-    plan->staged_pending = true;
+    SALT_HIP(ctx, hipEventRecord(plan->staged[stage], s));
+    plan->staged_pending[stage] = true;
   }
   return SALT_OK;
 }
@@ -433,8 +460,10 @@ salt_status build_impl(salt_ctx* ctx, salt_plan* plan, hipStream_t s) {
   if (plan->T > 0) {
     SALT_HIP(ctx, use_stream(ctx, plan, s));
     salt::PlanLaunch pl{};
-    pl.maps = plan->staged_dev;
+    const int4* host = plan->staging_dev + (size_t)plan->stage * plan->stage_len;
+    pl.maps = plan->in_place ? host : plan->staged_dev;
     pl.tiles = plan->staged_dev + plan->T;
+    pl.tiles_src = plan->in_place ? host + plan->T : nullptr;
     pl.keys = plan->keys;
     pl.keys_sorted = plan->keys + plan->max_T;
     pl.srt = plan->srt;
@@ -447,7 +476,14 @@ salt_status build_impl(salt_ctx* ctx, salt_plan* plan, hipStream_t s) {
     pl.T = plan->T;
     pl.n_tiles = plan->n_tiles + plan->n_stiles;              // both lists, checked alike
     pl.n_list0 = plan->n_tiles;
-    SALT_HIP(ctx, salt::launch_plan(pl, s));
+    salt::PlanArgs args;
+    if (plan->in_args)
+      std::copy_n(plan->staging + (size_t)plan->stage * plan->stage_len, pl.T + pl.n_tiles, args.e);
+    SALT_HIP(ctx, salt::launch_plan(pl, plan->in_args ? &args : nullptr, s));
+    if (plan->in_place) {
+      SALT_HIP(ctx, hipEventRecord(plan->staged[plan->stage], s));
+      plan->staged_pending[plan->stage] = true;
+    }
   }
   plan->built = true;
   return SALT_OK;
@@ -796,26 +832,19 @@ salt_status salt_create(const salt_config* cfg, salt_ctx** out) {
   size_t max_dim = 8;
   for (const salt_shape& s : c->tables) max_dim = std::max<size_t>(max_dim, std::max(s.in_dim, s.out_dim));
   const size_t zero_bytes = round_up(max_dim * c->esize, kAlign);
-  if (hipMalloc((void**)&c->zeros, zero_bytes) != hipSuccess) {
+  // the zero page and, behind it, the table records, in one copy
+  const size_t rec_bytes = c->tables.size() * sizeof(salt::GramTable);
+  std::vector<char> page(zero_bytes + rec_bytes, 0);
+  for (size_t t = 0; t < c->tables.size(); ++t) {
+    const salt::GramTable g{c->tab_prefix[t], c->tables[t].in_dim, c->tables[t].out_dim};
+    std::memcpy(page.data() + zero_bytes + t * sizeof g, &g, sizeof g);
+  }
+  if (hipMalloc((void**)&c->zeros, page.size()) != hipSuccess) {
     (void)hipGetLastError();
     return bail(SALT_ERR_OUT_OF_MEMORY, hipSuccess, "");
   }
-  std::vector<salt::GramTable> gt(c->tables.size());
-  for (size_t t = 0; t < gt.size(); ++t)
-    gt[t] = salt::GramTable{c->tab_prefix[t], c->tables[t].in_dim, c->tables[t].out_dim};
-  if (hipMalloc((void**)&c->gram_tabs, gt.size() * sizeof(salt::GramTable)) != hipSuccess) {
-    (void)hipGetLastError();
-    return bail(SALT_ERR_OUT_OF_MEMORY, hipSuccess, "");
-  }
-  if (hipHostMalloc((void**)&c->gram_out, gt.size() * 3 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    return bail(SALT_ERR_OUT_OF_MEMORY, hipSuccess, "");
-  }
-  e = hipHostGetDevicePointer((void**)&c->gram_out_dev, c->gram_out, 0);
-  if (e != hipSuccess) return bail(SALT_ERR_HIP, e, "Gram results");
-  e = hipMemcpy(c->gram_tabs, gt.data(), gt.size() * sizeof(salt::GramTable), hipMemcpyHostToDevice);
-  if (e != hipSuccess) return bail(SALT_ERR_HIP, e, "table records");
-  e = hipMemset(c->zeros, 0, zero_bytes);
+  c->gram_tabs = reinterpret_cast<salt::GramTable*>(c->zeros + zero_bytes);
+  e = hipMemcpy(c->zeros, page.data(), page.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) return bail(SALT_ERR_HIP, e, "zero page");
   c->slot_stride = round_up(std::max<size_t>(1, salt_residual_bytes(c, cfg->r_u_max)), kAlign);
@@ -1136,6 +1165,16 @@ salt_status salt_adapter_gram(salt_ctx* ctx, const void* blob1, int32_t r1, cons
       return fail(ctx, SALT_ERR_OUT_OF_MEMORY, "adapter Gram scratch (%zu bytes)", need);
     }
     ctx->gram_bytes = need;
+  }
+  if (!ctx->gram_out) {
+    void *p = nullptr, *d = nullptr;
+    if (hipHostMalloc(&p, sizeof(double) * 3 * nt, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(ctx, SALT_ERR_OUT_OF_MEMORY, "adapter Gram results");
+    }
+    ctx->gram_out = static_cast<double*>(p);
+    SALT_HIP(ctx, hipHostGetDevicePointer(&d, p, 0));
+    ctx->gram_out_dev = static_cast<double*>(d);
   }
   a.g = reinterpret_cast<float*>(ctx->gram);
   a.out = ctx->gram_out_dev;
