@@ -60,7 +60,7 @@ constexpr int threads_of() { return 64 * waves_of(M); }
 // spilling; other kernels keep the compiler's choice.
 template <typename E, int M, int NB, int RU>
 constexpr int expand_waves() {
-  return sizeof(E) == 2 && M == 128 && RU <= 2 && NB <= 4 ? (RU == 1 || NB == 0 ? 4 : 2) : 1;
+  return sizeof(E) == 2 && M == 128 && ((NB <= 2 && RU <= 2) || (NB <= 4 && RU <= 1)) ? 4 : 1;
 }
 template <typename E, int M, int NB>
 constexpr bool staged() { return sizeof(E) == 2 && M > 16 && NB > 0; }
@@ -1185,7 +1185,7 @@ void launch_k(K kernel, int blocks, int threads, size_t lds, hipStream_t s, cons
 }
 
 template <typename E, int M, int NB, int RU>
-auto shrink_kernel() {
+constexpr auto shrink_kernel() {
   if constexpr (RU > 2) return k_shrink_wide<E, NB>;
   else return k_shrink<E, M, NB, RU>;
 }
@@ -1207,8 +1207,9 @@ size_t expand_lds(int R) {
 
 // Blocks of `kernel` with `lds` bytes of LDS that one compute unit holds at once
 // (cached per kernel for the last LDS size asked).
-template <typename K>
-int resident_blocks(K kernel, int threads, size_t lds) {
+// (a template on the kernel itself: kernels share a type, and must not share the cache)
+template <auto kernel>
+int resident_blocks(int threads, size_t lds) {
   static std::atomic<uint64_t> cache{0};                     // (lds << 32) | blocks
   const uint64_t c = cache.load(std::memory_order_relaxed);
   if (c != 0 && (c >> 32) == (uint64_t)lds) return (int)(c & 0xffffffffu);
@@ -1231,13 +1232,12 @@ hipError_t launch_mnr(const ApplyLaunch& a, hipStream_t s, hipEvent_t* ev) {
   launch_k(shrink_kernel<E, MS, NB, RU>(), a.shrink_blocks, threads_of<MS>(), shrink_lds<E, MS, NB, RU>(), s, a,
            ev ? ev[0] : nullptr, ev ? ev[1] : nullptr);
   const size_t lds = expand_lds<E, M, NB, RU>(a.R);
-  const int round = resident_blocks(k_expand<E, M, NB, RU>, NT, lds) * std::max(1, a.n_cu);
+  const int round = resident_blocks<k_expand<E, M, NB, RU>>(NT, lds) * std::max(1, a.n_cu);
   // One round of blocks walks the items, an equal share each.  Where some tiles
   // hold ranks of several chunks an item costs as much as its tokens' ranks, and
   // equal shares would leave most of the device idle behind the blocks that got
   // the long ones (Zipf T = 512 with rank-65/66 users: 268 us): eight rounds,
-  // handed out as blocks finish (175 us).  Batches of one chunk (rank-16 LoRA)
-  // keep the one round: 64 us against 70 us.
+  // handed out as blocks finish (143 us).
   const int rounds = RU > 2 && a.n_pairs > a.n_stiles ? 8 : 1;
   const int grid = (int)std::min<int64_t>(a.expand_items, (int64_t)rounds * round);
   launch_k(k_expand<E, M, NB, RU>, grid, NT, lds, s, a, ev ? ev[2] : nullptr, ev ? ev[3] : nullptr);
@@ -1263,11 +1263,10 @@ hipError_t launch_m(const ApplyLaunch& a, hipStream_t s, hipEvent_t* ev) {
 
 template <typename E, int MS>
 int shrink_round_m(const ApplyLaunch& a) {
-  auto round = [&](auto kernel, size_t lds) { return resident_blocks(kernel, threads_of<MS>(), lds) * std::max(1, a.n_cu); };
   const int nb = centroid_blocks(a.r_c);
   const int ru = a.r_u <= 1 ? 1 : (a.r_u <= 2 ? 2 : kRankChunk);
 #define SALT_ROUND(NB_, RU_) \
-  if (nb == NB_ && ru == RU_) return round(shrink_kernel<E, MS, NB_, RU_>(), shrink_lds<E, MS, NB_, RU_>());
+  if (nb == NB_ && ru == RU_) return resident_blocks<shrink_kernel<E, MS, NB_, RU_>()>(threads_of<MS>(), shrink_lds<E, MS, NB_, RU_>()) * std::max(1, a.n_cu);
   SALT_ROUND(0, 1) SALT_ROUND(0, 2)
   SALT_ROUND(2, 1) SALT_ROUND(2, 2)
   SALT_ROUND(4, 1) SALT_ROUND(4, 2)

@@ -91,7 +91,11 @@ inline int max_tiles(int T, int C) { return cdiv(T, 16) + C + 1; }
 // shrink_round: shrink blocks one round of the device holds at once (0: unknown).
 inline bool configure_launch(ApplyLaunch& a, int n_cu, int n_groups_c, int64_t sum_rank, int shrink_round = 0) {
   const int KW = waves_of(a.MS) / (a.MS / 16), CW = waves_of(a.M) / (a.M / 16);
-  const int target = 8 * std::max(1, n_cu);        // blocks per launch: a few rounds of the whole device
+  // blocks per launch: a few rounds of the whole device; half as many, twice as
+  // long, where every block has one chunk of rows above rank 2 to stream (Zipf
+  // T = 512, rank-16 LoRA: 73 -> 63 us; with chunks of uneven tiles 136 -> 140 us)
+  const bool rows_only = a.r_u > 2 && a.n_pairs == a.n_stiles;
+  const int target = (rows_only ? 4 : 8) * std::max(1, n_cu);
   const double es = (double)a.esize;
   const double adapters = (double)n_groups_c * a.r_c + (double)sum_rank;
   int64_t sum_in = 0;

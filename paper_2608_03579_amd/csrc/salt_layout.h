@@ -293,12 +293,13 @@ SALT_HD int quad_elem(int lane) { return 32 * (lane >> 4) + 8 * (lane & 3); }
 // of every tile, holds of tiles 2 s and 2 s + 1 the columns 32 g + 8 s + 0..7.
 SALT_HD int quad_col(int i, int t) { return 32 * (i >> 2) + 4 * t + (i & 3); }
 
-// Whether the expand runs in the quad layout: 128-token tiles and residual ranks
-// above 2, whose time is the streams of rows themselves.  Smaller tiles of ranks
-// up to 2 keep the row layout, whose shorter chunks, two sets of operands and
+// Whether the expand runs in the quad layout: 128-token tiles of ranks up to 1 and
+// residual ranks above 2, whose time is the streams of rows themselves.  Smaller
+// tiles keep the row layout, whose shorter chunks, two sets of operands and
 // cheaper set-up serve short groups better (Llama-3.1-8B decode T = 256: 34.5 us
-// against 36 us, Zipf T = 512: 35 against 39, 64-token tiles of rank 2: 41
-// against 49).
-SALT_HD constexpr bool quad_expand(int M, int r_u) { return M == 128 || r_u > 2; }
+// against 36 us, Zipf T = 512: 35 against 39, 64-token tiles of rank 2: 41 against
+// 49), and so do 128-token tiles of rank 2, for whose second row the quad layout
+// has no registers left (prefill T = 8192, r_c = 64: 266 us against 291 us).
+SALT_HD constexpr bool quad_expand(int M, int r_u) { return (M == 128 && r_u <= 1) || r_u > 2; }
 
 }  // namespace salt
