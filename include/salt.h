@@ -176,8 +176,9 @@ SALT_API void salt_host_free(void* p);
  * Why four calls (create / set_maps / build / destroy) instead of one build
  * that allocates: a serving loop keeps one plan per stream and reuses its
  * buffers batch after batch, so no call on the hot path allocates; the maps
- * are staged (host validation, one H2D copy) separately from the device build
- * so that the copy can be issued early.  salt_apply_map is the one-shot form. */
+ * are staged (host validation) separately from the device build, so that the
+ * next batch can be staged while the last one runs.  salt_apply_map is the
+ * one-shot form. */
 SALT_API salt_status salt_plan_create(salt_ctx* ctx, salt_plan** out);
 SALT_API void salt_plan_destroy(salt_ctx* ctx, salt_plan* plan);
 
@@ -188,7 +189,9 @@ SALT_API void salt_plan_destroy(salt_ctx* ctx, salt_plan* plan);
  *                 NULL for gamma = 1.  Must be finite.
  * Validates the maps on the host (SALT_ERR_OUT_OF_RANGE, SALT_ERR_SLOT_EMPTY for
  * a slot never loaded), snapshots the residual rank of every referenced slot and
- * enqueues one H2D copy of the packed maps on `stream`.  0 <= T <= max_tokens;
+ * keeps the packed maps in a page-locked staging buffer, which the build reads;
+ * for T > 4096, and for a plan whose build was recorded into a graph, it enqueues
+ * one H2D copy of them on `stream`.  0 <= T <= max_tokens;
  * T == 0 gives an empty plan whose applies do nothing. */
 SALT_API salt_status salt_plan_set_maps(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32_t* tok_c,
                                const int32_t* tok_u, const float* tok_gamma, void* stream);

@@ -112,6 +112,11 @@ struct salt_plan {
   bool args_only = false;           // every batch travels in the kernel's arguments: the ring is ordinary memory
   bool in_place = false;            // the batch's builds read the staging buffer in place
   bool in_args = false;             // or carry it in the kernel's arguments
+  // A build recorded into a graph is replayed after later set_maps calls and must
+  // find their maps: from its first captured build on, the plan stages by copy,
+  // into staged_cap (in staged_dev's place; nothing in flight reads it then).
+  bool captured = false;
+  int4* staged_cap = nullptr;
   hipEvent_t hop = nullptr;         // orders the plan's work across streams
   int32_t max_T = 0, tile_cap = 0;
   // the batch
@@ -290,7 +295,7 @@ hipError_t use_stream(salt_ctx* ctx, salt_plan* plan, hipStream_t s) {
 }
 
 void free_plan(salt_plan* p) {
-  void* dev[] = {p->staged_dev, p->keys, p->srt, p->ints, p->meta, p->partials};
+  void* dev[] = {p->staged_dev, p->staged_cap, p->keys, p->srt, p->ints, p->meta, p->partials};
   for (void* q : dev)
     if (q) (void)hipFree(q);
   if (p->args_only) delete[] p->staging;
@@ -328,6 +333,7 @@ salt_status plan_create(salt_ctx* ctx, salt_plan** out) {
   const size_t staged = T + 2 * (size_t)p->tile_cap;
   p->args_only = T <= (size_t)salt::kArgTokens && staged <= (size_t)salt::kArgEntries;
   bool ok = hipMalloc((void**)&p->staged_dev, staged * sizeof(int4)) == hipSuccess &&
+            hipMalloc((void**)&p->staged_cap, staged * sizeof(int4)) == hipSuccess &&
             hipMalloc((void**)&p->keys, 2 * T * sizeof(uint64_t)) == hipSuccess &&
             hipMalloc((void**)&p->srt, T * sizeof(int4)) == hipSuccess &&
             hipMalloc((void**)&p->ints, salt_plan::n_ints(T) * 4) == hipSuccess &&
@@ -435,8 +441,8 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
   std::copy(tiles.begin(), tiles.end(), staging + T);
   std::copy(stiles.begin(), stiles.end(), staging + T + tiles.size());
   plan->stage = stage;
-  plan->in_args = T <= salt::kArgTokens && T + (int)(tiles.size() + stiles.size()) <= salt::kArgEntries;
-  plan->in_place = !plan->in_args && T <= salt::kInPlaceTokens;
+  plan->in_args = !plan->captured && T <= salt::kArgTokens && T + (int)(tiles.size() + stiles.size()) <= salt::kArgEntries;
+  plan->in_place = !plan->captured && !plan->in_args && T <= salt::kInPlaceTokens;
   plan->n_tiles = (int32_t)tiles.size();
   plan->n_stiles = (int32_t)stiles.size();
   plan->n_groups_c = n_groups_c;
@@ -448,10 +454,31 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
     SALT_HIP(ctx, use_stream(ctx, plan, s));
     SALT_HIP(ctx, hipMemcpyAsync(plan->staged_dev, staging,
                                  ((size_t)T + tiles.size() + stiles.size()) * sizeof(int4), hipMemcpyHostToDevice, s));
+    if (!plan->staged[stage]) SALT_HIP(ctx, hipEventCreateWithFlags(&plan->staged[stage], hipEventDisableTiming));
     SALT_HIP(ctx, hipEventRecord(plan->staged[stage], s));
     plan->staged_pending[stage] = true;
   }
   return SALT_OK;
+}
+
+// The staged batch into staged_cap, on the side stream and waited for, beside a
+// capture on another stream (whose mode forbids such calls to this thread unless
+// it is relaxed meanwhile).
+hipError_t stage_for_capture(salt_ctx* ctx, salt_plan* plan) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) return e;
+  const size_t n = (size_t)plan->T + plan->n_tiles + plan->n_stiles;
+  e = hipMemcpyAsync(plan->staged_cap, plan->staging + (size_t)plan->stage * plan->stage_len, n * sizeof(int4),
+                     hipMemcpyHostToDevice, ctx->side);
+  if (e == hipSuccess) e = hipStreamSynchronize(ctx->side);
+  const hipError_t r = hipThreadExchangeStreamCaptureMode(&mode);
+  if (e == hipSuccess) e = r;
+  if (e != hipSuccess) return e;
+  std::swap(plan->staged_dev, plan->staged_cap);
+  plan->captured = true;
+  plan->in_args = plan->in_place = false;
+  return hipSuccess;
 }
 
 salt_status build_impl(salt_ctx* ctx, salt_plan* plan, hipStream_t s) {
@@ -459,6 +486,11 @@ salt_status build_impl(salt_ctx* ctx, salt_plan* plan, hipStream_t s) {
   SALT_HIP(ctx, hipSetDevice(ctx->device));
   if (plan->T > 0) {
     SALT_HIP(ctx, use_stream(ctx, plan, s));
+    if (plan->in_args || plan->in_place) {
+      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+      else if (cap == hipStreamCaptureStatusActive) SALT_HIP(ctx, stage_for_capture(ctx, plan));
+    }
     salt::PlanLaunch pl{};
     const int4* host = plan->staging_dev + (size_t)plan->stage * plan->stage_len;
     pl.maps = plan->in_place ? host : plan->staged_dev;
