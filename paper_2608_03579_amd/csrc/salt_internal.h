@@ -18,7 +18,7 @@ enum Meta { kMetaNSeg = 0, kMetaNGrp = 1, kMetaT = 2, kMetaNTiles = 3, kMetaErr 
 struct PlanLaunch {
   const int4* maps;     // [T] staged maps: (c, u, r, gamma bits) by token
   int4* tiles;          // [n_tiles] tile headers (i0, n, c, largest rank), on the device
-  const int4* tiles_src;// null, or where the build copies them from: the host's staging buffer, as are maps then
+  const int4* tiles_src;// null, or where the build copies them from (maps + T; up to kSortChunk tokens)
   uint64_t* keys;       // [T] chunk-sorted keys (batches of more than one chunk)
   uint64_t* keys_sorted;// [T] sorted keys (idem)
   int4* srt;            // [T] (token, slot, rank, gamma bits) at each place

@@ -113,10 +113,15 @@ struct salt_plan {
   bool in_place = false;            // the batch's builds read the staging buffer in place
   bool in_args = false;             // or carry it in the kernel's arguments
   // A build recorded into a graph is replayed after later set_maps calls and must
-  // find their maps: from its first captured build on, the plan stages by copy,
-  // into staged_cap (in staged_dev's place; nothing in flight reads it then).
+  // find their maps, and graphs keep the addresses they were recorded with, so no
+  // buffer ever takes another's place: the applies' tiles stand at staged_dev + T
+  // for good, and from its first captured build of up to kInPlaceTokens tokens on,
+  // the plan stages such batches by copy into staged_cap, whose tiles the build
+  // copies to staged_dev + T (nothing in flight reads staged_cap at that first
+  // build).  Larger batches are copied into staged_dev, captured or not.
   bool captured = false;
   int4* staged_cap = nullptr;
+  bool fixed = false;               // the batch's maps and tiles are copied into staged_cap
   hipEvent_t hop = nullptr;         // orders the plan's work across streams
   int32_t max_T = 0, tile_cap = 0;
   // the batch
@@ -443,6 +448,7 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
   plan->stage = stage;
   plan->in_args = !plan->captured && T <= salt::kArgTokens && T + (int)(tiles.size() + stiles.size()) <= salt::kArgEntries;
   plan->in_place = !plan->captured && !plan->in_args && T <= salt::kInPlaceTokens;
+  plan->fixed = plan->captured && T <= salt::kInPlaceTokens;
   plan->n_tiles = (int32_t)tiles.size();
   plan->n_stiles = (int32_t)stiles.size();
   plan->n_groups_c = n_groups_c;
@@ -452,7 +458,7 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
   plan->built = false;
   if (T > 0 && !plan->in_place && !plan->in_args) {
     SALT_HIP(ctx, use_stream(ctx, plan, s));
-    SALT_HIP(ctx, hipMemcpyAsync(plan->staged_dev, staging,
+    SALT_HIP(ctx, hipMemcpyAsync(plan->fixed ? plan->staged_cap : plan->staged_dev, staging,
                                  ((size_t)T + tiles.size() + stiles.size()) * sizeof(int4), hipMemcpyHostToDevice, s));
     if (!plan->staged[stage]) SALT_HIP(ctx, hipEventCreateWithFlags(&plan->staged[stage], hipEventDisableTiming));
     SALT_HIP(ctx, hipEventRecord(plan->staged[stage], s));
@@ -475,8 +481,7 @@ hipError_t stage_for_capture(salt_ctx* ctx, salt_plan* plan) {
   const hipError_t r = hipThreadExchangeStreamCaptureMode(&mode);
   if (e == hipSuccess) e = r;
   if (e != hipSuccess) return e;
-  std::swap(plan->staged_dev, plan->staged_cap);
-  plan->captured = true;
+  plan->captured = plan->fixed = true;
   plan->in_args = plan->in_place = false;
   return hipSuccess;
 }
@@ -493,9 +498,9 @@ salt_status build_impl(salt_ctx* ctx, salt_plan* plan, hipStream_t s) {
     }
     salt::PlanLaunch pl{};
     const int4* host = plan->staging_dev + (size_t)plan->stage * plan->stage_len;
-    pl.maps = plan->in_place ? host : plan->staged_dev;
+    pl.maps = plan->in_place ? host : (plan->fixed ? plan->staged_cap : plan->staged_dev);
     pl.tiles = plan->staged_dev + plan->T;
-    pl.tiles_src = plan->in_place ? host + plan->T : nullptr;
+    pl.tiles_src = plan->in_place || plan->fixed ? pl.maps + plan->T : nullptr;
     pl.keys = plan->keys;
     pl.keys_sorted = plan->keys + plan->max_T;
     pl.srt = plan->srt;

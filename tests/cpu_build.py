@@ -2,7 +2,8 @@
 CPU against ``tests/cpu_kernels/hip``), run under AddressSanitizer.
 
 ``build()`` compiles the sources with the host clang of ROCm, once per source
-hash, into ``tests/cpu_kernels/_build/harness``.  The only change made to a
+hash, into ``tests/cpu_kernels/_build/harness`` (and, beside it, the programs of
+PROGRAMS, which drive the same library through their own sequences).  The only change made to a
 source is the declaration of the dynamic LDS array, which becomes a pointer to
 the exact-size buffer the host runtime allocates for each launch.  ``run()``
 writes a run description (context, pinned centroids, residual loads, batches),
@@ -29,6 +30,7 @@ SHIM = os.path.join(HERE, "cpu_kernels")
 BUILD = os.path.join(SHIM, "_build")
 SOURCES = ("salt_plan.hip", "salt_apply.hip", "salt_fuse_gram.hip", "salt_swap.hip", "salt_runtime.cpp")
 HEADERS = ("salt_device.h", "salt_internal.h", "salt_layout.h", "salt_launch.h")
+PROGRAMS = ("capture",)          # tests/cpu_kernels/<name>.cpp
 DYN_LDS = "extern __shared__ __attribute__((aligned(16))) char lds[];"
 CLANG = "/opt/rocm/llvm/bin/clang++"
 
@@ -39,7 +41,8 @@ def available() -> bool:
 
 def _digest() -> str:
     h = hashlib.sha256()
-    for d, names in ((CSRC, SOURCES + HEADERS), (SHIM, ("harness.cpp", "hip/hip_runtime.h", "hip/hip_ext.h"))):
+    for d, names in ((CSRC, SOURCES + HEADERS), (SHIM, ("harness.cpp", "hip/hip_runtime.h", "hip/hip_ext.h") +
+                                                           tuple(n + ".cpp" for n in PROGRAMS))):
         for n in names:
             h.update(n.encode())
             h.update(open(os.path.join(d, n), "rb").read())
@@ -71,23 +74,35 @@ def _build(exe: str) -> str:
         text = text.replace(DYN_LDS, "char* lds = salt_cpu::g_dyn_lds;")
         with open(os.path.join(src, n), "w") as f:
             f.write(text)
-    srcs = [os.path.join(src, n) for n in SOURCES] + [os.path.join(SHIM, "harness.cpp")]
+    mains = [os.path.join(SHIM, n + ".cpp") for n in ("harness",) + PROGRAMS]
+    srcs = [os.path.join(src, n) for n in SOURCES] + mains
     flags = ["-std=c++17", "-O1", "-g", "-fsanitize=address", "-fno-omit-frame-pointer", "-w"]
     for old in os.listdir(BUILD):
-        if old.startswith("harness-") and old != os.path.basename(exe):
+        if "-" in old and not old.endswith(os.path.basename(exe).split("-")[1]):
             os.remove(os.path.join(BUILD, old))
-    # one compiler process per source, then one link
+    # one compiler process per source, then one link per program (the harness last)
     objs = [os.path.join(src, os.path.basename(s) + ".o") for s in srcs]
     procs = [subprocess.Popen([CLANG, *flags, f"-I{SHIM}", f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}",
                                "-x", "c++", "-c", s, "-o", o], stdout=subprocess.PIPE, stderr=subprocess.PIPE,
                               text=True) for s, o in zip(srcs, objs)]
     errs = [(p.communicate()[1], p.returncode) for p in procs]
-    res = subprocess.run([CLANG, *flags, *objs, "-o", exe + ".tmp"], capture_output=True, text=True)
-    if any(rc for _, rc in errs) or res.returncode != 0:
-        msg = "".join(e for e, rc in errs if rc) + res.stderr
+    lib, links = objs[:len(SOURCES)], []
+    for n, o in reversed(list(zip(("harness",) + PROGRAMS, objs[len(SOURCES):]))):
+        out = exe.replace("harness-", n + "-")
+        links.append(subprocess.run([CLANG, *flags, *lib, o, "-o", out + ".tmp"], capture_output=True, text=True))
+        if links[-1].returncode == 0:
+            os.replace(out + ".tmp", out)
+    if any(rc for _, rc in errs) or any(l.returncode for l in links):
+        msg = "".join(e for e, rc in errs if rc) + "".join(l.stderr for l in links)
         raise RuntimeError("host build of libsalt failed:\n" + msg[-6000:])
-    os.replace(exe + ".tmp", exe)
     return exe
+
+
+def program(name: str, *args: str) -> subprocess.CompletedProcess:
+    """Builds, and runs the program `name` under AddressSanitizer."""
+    exe = build().replace("harness-", name + "-")
+    return subprocess.run([exe, *args], capture_output=True, text=True, timeout=600,
+                          env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=0"))
 
 
 class Batch:

@@ -28,6 +28,7 @@
 
 #include <functional>
 #include <map>
+#include <utility>
 #include <vector>
 
 #if defined(__has_feature)
@@ -89,7 +90,9 @@ typedef enum {
   hipErrorInvalidConfiguration = 9,
   hipErrorInvalidDevice = 101,
   hipErrorInvalidSymbol = 13,
-  hipErrorLaunchFailure = 719
+  hipErrorLaunchFailure = 719,
+  hipErrorStreamCaptureUnsupported = 900,
+  hipErrorCapturedEvent = 907
 } hipError_t;
 typedef struct salt_cpu_stream* hipStream_t;
 typedef struct salt_cpu_event* hipEvent_t;
@@ -346,7 +349,6 @@ inline int salt_cpu_update_dpp(int, int v, int ctrl, int, int, bool) {
   return salt_cpu::wave_xchg(v, (l & ~3) | ((ctrl >> (2 * (l & 3))) & 3));
 }
 #define __builtin_amdgcn_update_dpp salt_cpu_update_dpp
-#define __builtin_amdgcn_sched_barrier(mask)   // an order hint for the GPU compiler only
 inline int atomicAdd(int* p, int v) {
   const int o = *p;
   *p = o + v;
@@ -479,7 +481,44 @@ inline hipError_t hipGetDevice(int* d) {
   *d = 0;
   return hipSuccess;
 }
-inline hipError_t hipDeviceSynchronize() { return hipSuccess; }
+// Stream capture: while `stream` is recorded, work sent to it becomes nodes, run in
+// order by each launch of the graph.  Calls that would wait for the device or
+// allocate are refused meanwhile unless the thread's mode is relaxed (waiting for
+// an event is refused in any mode), as the HIP runtime refuses them.
+enum hipStreamCaptureMode { hipStreamCaptureModeGlobal, hipStreamCaptureModeThreadLocal, hipStreamCaptureModeRelaxed };
+enum hipStreamCaptureStatus { hipStreamCaptureStatusNone, hipStreamCaptureStatusActive };
+namespace salt_cpu {
+using Graph = std::vector<std::function<void()>>;
+struct Capture {
+  Graph* graph = nullptr;                       // null: no capture
+  hipStream_t stream = nullptr;
+  hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
+};
+inline Capture g_capture;
+inline bool recording(hipStream_t s) { return g_capture.graph && g_capture.stream == s; }
+inline bool forbidden() { return g_capture.graph && g_capture.mode != hipStreamCaptureModeRelaxed; }
+}  // namespace salt_cpu
+inline hipError_t hipDeviceSynchronize() {
+  return salt_cpu::g_capture.graph ? hipErrorStreamCaptureUnsupported : hipSuccess;
+}
+inline hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) {
+  std::swap(*m, salt_cpu::g_capture.mode);
+  return hipSuccess;
+}
+inline hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* st) {
+  *st = salt_cpu::recording(s) ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+// (tests only: begin and end a capture, and launch what was recorded)
+inline void salt_cpu_begin_capture(hipStream_t s) { salt_cpu::g_capture = {new salt_cpu::Graph(), s}; }
+inline salt_cpu::Graph* salt_cpu_end_capture() {
+  salt_cpu::Graph* g = salt_cpu::g_capture.graph;
+  salt_cpu::g_capture = {};
+  return g;
+}
+inline void salt_cpu_replay(const salt_cpu::Graph& g) {
+  for (const auto& node : g) node();
+}
 template <typename F>
 inline hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, F, int, size_t) {
   *n = 2;
@@ -490,6 +529,7 @@ inline hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
   return hipSuccess;
 }
 inline hipError_t hipMalloc(void** p, size_t n) {
+  if (salt_cpu::forbidden()) return hipErrorStreamCaptureUnsupported;
   *p = salt_cpu::alloc(n, false);
   return *p ? hipSuccess : hipErrorOutOfMemory;
 }
@@ -517,14 +557,21 @@ inline hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
   if (n) memcpy(d, s, n);
   return hipSuccess;
 }
-inline hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t) {
+inline hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t st) {
+  if (salt_cpu::recording(st)) {
+    salt_cpu::g_capture.graph->push_back([=] { memcpy(d, s, n); });
+    return hipSuccess;
+  }
   return hipMemcpy(d, s, n, k);
 }
 inline hipError_t hipMemset(void* d, int v, size_t n) {
   if (n) memset(d, v, n);
   return hipSuccess;
 }
-inline hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) { return hipMemset(d, v, n); }
+inline hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t s) {
+  if (salt_cpu::recording(s)) return hipErrorStreamCaptureUnsupported;   // (not in a graph: libsalt records none)
+  return hipMemset(d, v, n);
+}
 inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
   *s = reinterpret_cast<hipStream_t>(new int(0));
   return hipSuccess;
@@ -533,17 +580,12 @@ inline hipError_t hipStreamDestroy(hipStream_t s) {
   delete reinterpret_cast<int*>(s);
   return hipSuccess;
 }
-inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-enum hipStreamCaptureMode { hipStreamCaptureModeGlobal, hipStreamCaptureModeThreadLocal, hipStreamCaptureModeRelaxed };
-enum hipStreamCaptureStatus { hipStreamCaptureStatusNone, hipStreamCaptureStatusActive };
-inline hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*) { return hipSuccess; }
-inline hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
-  *s = hipStreamCaptureStatusNone;
-  return hipSuccess;
+inline hipError_t hipStreamSynchronize(hipStream_t s) {
+  return salt_cpu::forbidden() || salt_cpu::recording(s) ? hipErrorStreamCaptureUnsupported : hipSuccess;
 }
 inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
-  *e = reinterpret_cast<hipEvent_t>(new int(0));
+  *e = reinterpret_cast<hipEvent_t>(new int(0));        // (1: recorded into a capture)
   return hipSuccess;
 }
 inline hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
@@ -551,8 +593,13 @@ inline hipError_t hipEventDestroy(hipEvent_t e) {
   delete reinterpret_cast<int*>(e);
   return hipSuccess;
 }
-inline hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
-inline hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+  *reinterpret_cast<int*>(e) = salt_cpu::recording(s);
+  return hipSuccess;
+}
+inline hipError_t hipEventSynchronize(hipEvent_t e) {
+  return salt_cpu::g_capture.graph || *reinterpret_cast<int*>(e) ? hipErrorCapturedEvent : hipSuccess;
+}
 inline hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
   const salt_cpu::Alloc* al = salt_cpu::find(p);
   if (!al) return hipErrorInvalidValue;
@@ -564,8 +611,12 @@ inline hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* 
 }
 
 template <typename... KArgs, typename... Args>
-inline void hipLaunchKernelGGL(void (*k)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t,
+inline void hipLaunchKernelGGL(void (*k)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t s,
                                Args&&... args) {
+  if (salt_cpu::recording(s)) {
+    salt_cpu::g_capture.graph->push_back([=] { salt_cpu::launch(grid, block, lds, [&]() { k(args...); }); });
+    return;
+  }
   salt_cpu::launch(grid, block, lds, [&]() { k(args...); });
 }
 template <typename... KArgs, typename... Args>
