@@ -191,7 +191,9 @@ SALT_API void salt_plan_destroy(salt_ctx* ctx, salt_plan* plan);
  * a slot never loaded), snapshots the residual rank of every referenced slot and
  * keeps the packed maps in a page-locked staging buffer, which the build reads;
  * for T > 4096, and for a plan whose build was recorded into a graph, it enqueues
- * one H2D copy of them on `stream`.  0 <= T <= max_tokens;
+ * one H2D copy of them on `stream`.  On a stream under capture it records nothing
+ * (replays of a recorded build serve the maps set last) and is refused for a plan
+ * that had maps before (SALT_ERR_BAD_STATE).  0 <= T <= max_tokens;
  * T == 0 gives an empty plan whose applies do nothing. */
 SALT_API salt_status salt_plan_set_maps(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32_t* tok_c,
                                const int32_t* tok_u, const float* tok_gamma, void* stream);

@@ -122,6 +122,9 @@ struct salt_plan {
   bool captured = false;
   int4* staged_cap = nullptr;
   bool fixed = false;               // the batch's maps and tiles are copied into staged_cap
+  // Maps set while their stream is recorded: the graph holds no copy of them (a
+  // replay would fetch whatever the staging buffer holds by then); the build copies.
+  bool deferred = false;
   hipEvent_t hop = nullptr;         // orders the plan's work across streams
   int32_t max_T = 0, tile_cap = 0;
   // the batch
@@ -373,6 +376,53 @@ salt_status plan_create(salt_ctx* ctx, salt_plan** out) {
   return SALT_OK;
 }
 
+// Whether work sent to `s` is being recorded into a graph.
+bool is_capturing(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cap == hipStreamCaptureStatusActive;
+}
+
+// The staged batch to where its builds read it from, on `s`.
+hipError_t copy_staged(salt_plan* plan, int4* dst, hipStream_t s) {
+  const size_t n = (size_t)plan->T + plan->n_tiles + plan->n_stiles;
+  return hipMemcpyAsync(dst, plan->staging + (size_t)plan->stage * plan->stage_len, n * sizeof(int4),
+                        hipMemcpyHostToDevice, s);
+}
+
+// The same ahead of a plan's build on `s`, with the event behind which the host
+// may write the staging buffer again.
+hipError_t enqueue_staged(salt_plan* plan, hipStream_t s) {
+  hipError_t e = copy_staged(plan, plan->fixed ? plan->staged_cap : plan->staged_dev, s);
+  hipEvent_t& ev = plan->staged[plan->stage];
+  if (e == hipSuccess && !ev) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventRecord(ev, s);
+  if (e == hipSuccess) plan->staged_pending[plan->stage] = true;
+  return e;
+}
+
+// The staged batch on the device, on the side stream and waited for, beside a
+// capture on another stream (whose mode forbids such calls to this thread unless
+// it is relaxed meanwhile).  Nothing in flight reads the destination: staged_cap at
+// the plan's first captured build, staged_dev on a plan no work was sent for yet.
+hipError_t stage_for_capture(salt_ctx* ctx, salt_plan* plan) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) return e;
+  const bool small = plan->T <= salt::kInPlaceTokens;
+  e = copy_staged(plan, small ? plan->staged_cap : plan->staged_dev, ctx->side);
+  if (e == hipSuccess) e = hipStreamSynchronize(ctx->side);
+  const hipError_t r = hipThreadExchangeStreamCaptureMode(&mode);
+  if (e == hipSuccess) e = r;
+  if (e != hipSuccess) return e;
+  if (small) plan->captured = plan->fixed = true;
+  plan->in_args = plan->in_place = plan->deferred = false;
+  return hipSuccess;
+}
+
 salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32_t* tok_c, const int32_t* tok_u,
                           const float* tok_gamma, hipStream_t s) {
   if (T < 0 || T > plan->max_T)
@@ -390,6 +440,11 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
       return fail(ctx, SALT_ERR_INVALID_ARG, "tok_gamma[%d] is not finite", t);
   }
   SALT_HIP(ctx, hipSetDevice(ctx->device));
+  // A graph can hold the maps of a plan's first batch only: those of a later one
+  // would be staged over buffers that the work recorded or enqueued before reads.
+  const bool capturing = is_capturing(s);
+  if (capturing && (plan->T > 0 || plan->used))
+    return fail(ctx, SALT_ERR_BAD_STATE, "maps set on a stream under capture, on a plan that had maps before");
   // the next staging buffer may still feed an earlier batch's copy or build
   const int stage = (plan->stage + 1) % kStageRing;
   if (plan->staged_pending[stage]) {
@@ -456,34 +511,12 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
   plan->sum_rank = sum_rank;
   plan->T = T;
   plan->built = false;
-  if (T > 0 && !plan->in_place && !plan->in_args) {
+  plan->deferred = capturing && T > 0;
+  if (T > 0 && !plan->in_place && !plan->in_args && !plan->deferred) {
     SALT_HIP(ctx, use_stream(ctx, plan, s));
-    SALT_HIP(ctx, hipMemcpyAsync(plan->fixed ? plan->staged_cap : plan->staged_dev, staging,
-                                 ((size_t)T + tiles.size() + stiles.size()) * sizeof(int4), hipMemcpyHostToDevice, s));
-    if (!plan->staged[stage]) SALT_HIP(ctx, hipEventCreateWithFlags(&plan->staged[stage], hipEventDisableTiming));
-    SALT_HIP(ctx, hipEventRecord(plan->staged[stage], s));
-    plan->staged_pending[stage] = true;
+    SALT_HIP(ctx, enqueue_staged(plan, s));
   }
   return SALT_OK;
-}
-
-// The staged batch into staged_cap, on the side stream and waited for, beside a
-// capture on another stream (whose mode forbids such calls to this thread unless
-// it is relaxed meanwhile).
-hipError_t stage_for_capture(salt_ctx* ctx, salt_plan* plan) {
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
-  if (e != hipSuccess) return e;
-  const size_t n = (size_t)plan->T + plan->n_tiles + plan->n_stiles;
-  e = hipMemcpyAsync(plan->staged_cap, plan->staging + (size_t)plan->stage * plan->stage_len, n * sizeof(int4),
-                     hipMemcpyHostToDevice, ctx->side);
-  if (e == hipSuccess) e = hipStreamSynchronize(ctx->side);
-  const hipError_t r = hipThreadExchangeStreamCaptureMode(&mode);
-  if (e == hipSuccess) e = r;
-  if (e != hipSuccess) return e;
-  plan->captured = plan->fixed = true;
-  plan->in_args = plan->in_place = false;
-  return hipSuccess;
 }
 
 salt_status build_impl(salt_ctx* ctx, salt_plan* plan, hipStream_t s) {
@@ -491,10 +524,11 @@ salt_status build_impl(salt_ctx* ctx, salt_plan* plan, hipStream_t s) {
   SALT_HIP(ctx, hipSetDevice(ctx->device));
   if (plan->T > 0) {
     SALT_HIP(ctx, use_stream(ctx, plan, s));
-    if (plan->in_args || plan->in_place) {
-      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-      if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-      else if (cap == hipStreamCaptureStatusActive) SALT_HIP(ctx, stage_for_capture(ctx, plan));
+    if ((plan->in_args || plan->in_place || plan->deferred) && is_capturing(s))
+      SALT_HIP(ctx, stage_for_capture(ctx, plan));
+    if (plan->deferred) {                                    // (built outside the capture after all)
+      if (!plan->in_args && !plan->in_place) SALT_HIP(ctx, enqueue_staged(plan, s));
+      plan->deferred = false;
     }
     salt::PlanLaunch pl{};
     const int4* host = plan->staging_dev + (size_t)plan->stage * plan->stage_len;

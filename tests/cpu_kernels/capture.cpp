@@ -1,5 +1,5 @@
-// Plan builds and applies recorded into graphs, on a host build of libsalt: the
-// sequence named by argv[1] with argv[2] tokens, every replay compared with the
+// Plan builds and applies recorded into graphs or left in flight, on a host build of
+// libsalt: the sequence named by argv[1] with argv[2] tokens, every replay compared with the
 // eager result of the same maps (integer inputs, bit for bit).  The maps differ
 // in their group sizes, at equal tile counts, as a graph's launches need.
 // Prints "ok" or the first difference.  Test infrastructure only.
@@ -162,6 +162,52 @@ int main(int argc, char** argv) {
         salt_cpu_replay(*g[i]);
         need(b.y == (i ? want_small : want)[(size_t)k], i ? "small batch" : "large batch", k);
       }
+  } else if (!strcmp(seq, "maps_in_capture")) {
+    // the maps of a fresh plan set inside the capture; a second batch there is
+    // refused and leaves plan, context and capture as they were
+    salt_cpu_begin_capture(b.s);
+    need(b.set(maps[0]) == SALT_OK, "captured set");
+    need(b.build() == SALT_OK && b.apply() == SALT_OK, "captured build and apply");
+    need(b.set(maps[1]) == SALT_ERR_BAD_STATE, "a second batch in the capture");
+    need(b.apply() == SALT_OK, "captured apply");
+    salt_cpu::Graph* g = salt_cpu_end_capture();
+    g->pop_back(), g->pop_back();                 // (the second apply's two launches)
+    int last = 0;
+    for (int k : {-1, -1, 1, 2, -1, 0, 1}) {      // (-1: no new maps)
+      if (k >= 0) need(b.set(maps[last = k]) == SALT_OK, "set");
+      b.reset();
+      salt_cpu_replay(*g);
+      same(last, "replay");
+    }
+    salt_cpu_begin_capture(b.s);
+    need(b.set(maps[0]) == SALT_ERR_BAD_STATE, "maps in a second capture");
+    salt_cpu_end_capture();
+    need(b.eager(maps[2]) == want[2], "eager after the captures");
+  } else if (!strcmp(seq, "batches_in_flight")) {
+    // many batches of one plan, none waited for by the caller: each must find its
+    // own maps in the staging buffers; and no event stands between a build and the
+    // shrink behind it
+    salt_cpu::g_lazy = true;
+    std::vector<std::vector<uint16_t>> ys(9, b.y0);
+    for (int i = 0; i < 9; ++i) {
+      need(b.set(maps[i % 3]) == SALT_OK, "set", i);
+      const int events = salt_cpu::g_events_recorded;
+      need(b.build() == SALT_OK, "build", i);
+      if (i == 4) need(b.build() == SALT_OK, "second build", i);
+      need(salt_apply(b.ctx, 0, b.plan, b.x.data(), ys[i].data(), b.s) == SALT_OK, "apply", i);
+      need(salt_cpu::g_events_recorded == events, "an event among build and apply", i);
+    }
+    need(hipStreamSynchronize(b.s) == hipSuccess, "synchronize");
+    for (int i = 0; i < 9; ++i) need(ys[i] == want[i % 3], "batch", i);
+    salt_cpu::g_lazy = false;
+  } else if (!strcmp(seq, "maps_in_capture_built_outside")) {
+    salt_cpu_begin_capture(b.s);
+    need(b.set(maps[0]) == SALT_OK, "captured set");
+    salt_cpu_end_capture();
+    b.reset();
+    need(b.build() == SALT_OK && b.apply() == SALT_OK, "eager build");
+    same(0, "eager build of captured maps");
+    need(b.eager(maps[1]) == want[1], "eager after it");
   } else {
     need(false, "no such sequence");
   }

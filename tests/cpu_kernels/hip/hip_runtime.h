@@ -495,11 +495,28 @@ struct Capture {
   hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
 };
 inline Capture g_capture;
+// Lazy streams: enqueued work runs only when the host waits for it (all streams in
+// one order, that of the calls), so that what the host overwrites too early shows.
+inline bool g_lazy = false;
+inline std::vector<std::function<void()>> g_queue;
+inline size_t g_ran = 0;                        // nodes of g_queue already run
+inline int g_events_recorded = 0;
+inline void run_queue(size_t end) {
+  for (; g_ran < end; ++g_ran) g_queue[g_ran]();
+}
 inline bool recording(hipStream_t s) { return g_capture.graph && g_capture.stream == s; }
 inline bool forbidden() { return g_capture.graph && g_capture.mode != hipStreamCaptureModeRelaxed; }
+// Work for stream `s`: recorded, queued or run.
+inline void enqueue(hipStream_t s, std::function<void()> f) {
+  if (recording(s)) g_capture.graph->push_back(std::move(f));
+  else if (g_lazy) g_queue.push_back(std::move(f));
+  else f();
+}
 }  // namespace salt_cpu
 inline hipError_t hipDeviceSynchronize() {
-  return salt_cpu::g_capture.graph ? hipErrorStreamCaptureUnsupported : hipSuccess;
+  if (salt_cpu::g_capture.graph) return hipErrorStreamCaptureUnsupported;
+  salt_cpu::run_queue(salt_cpu::g_queue.size());
+  return hipSuccess;
 }
 inline hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) {
   std::swap(*m, salt_cpu::g_capture.mode);
@@ -517,7 +534,7 @@ inline salt_cpu::Graph* salt_cpu_end_capture() {
   return g;
 }
 inline void salt_cpu_replay(const salt_cpu::Graph& g) {
-  for (const auto& node : g) node();
+  for (const auto& node : g) salt_cpu::enqueue(nullptr, node);
 }
 template <typename F>
 inline hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, F, int, size_t) {
@@ -554,15 +571,13 @@ inline hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) {
   return hipSuccess;
 }
 inline hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+  salt_cpu::run_queue(salt_cpu::g_queue.size());
   if (n) memcpy(d, s, n);
   return hipSuccess;
 }
-inline hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t st) {
-  if (salt_cpu::recording(st)) {
-    salt_cpu::g_capture.graph->push_back([=] { memcpy(d, s, n); });
-    return hipSuccess;
-  }
-  return hipMemcpy(d, s, n, k);
+inline hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
+  if (n) salt_cpu::enqueue(st, [=] { memcpy(d, s, n); });
+  return hipSuccess;
 }
 inline hipError_t hipMemset(void* d, int v, size_t n) {
   if (n) memset(d, v, n);
@@ -570,7 +585,8 @@ inline hipError_t hipMemset(void* d, int v, size_t n) {
 }
 inline hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t s) {
   if (salt_cpu::recording(s)) return hipErrorStreamCaptureUnsupported;   // (not in a graph: libsalt records none)
-  return hipMemset(d, v, n);
+  if (n) salt_cpu::enqueue(s, [=] { memset(d, v, n); });
+  return hipSuccess;
 }
 inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
   *s = reinterpret_cast<hipStream_t>(new int(0));
@@ -581,11 +597,13 @@ inline hipError_t hipStreamDestroy(hipStream_t s) {
   return hipSuccess;
 }
 inline hipError_t hipStreamSynchronize(hipStream_t s) {
-  return salt_cpu::forbidden() || salt_cpu::recording(s) ? hipErrorStreamCaptureUnsupported : hipSuccess;
+  if (salt_cpu::forbidden() || salt_cpu::recording(s)) return hipErrorStreamCaptureUnsupported;
+  salt_cpu::run_queue(salt_cpu::g_queue.size());
+  return hipSuccess;
 }
 inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
-  *e = reinterpret_cast<hipEvent_t>(new int(0));        // (1: recorded into a capture)
+  *e = reinterpret_cast<hipEvent_t>(new int(0));        // (-1: recorded into a capture; else the queue's length then)
   return hipSuccess;
 }
 inline hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
@@ -594,11 +612,15 @@ inline hipError_t hipEventDestroy(hipEvent_t e) {
   return hipSuccess;
 }
 inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
-  *reinterpret_cast<int*>(e) = salt_cpu::recording(s);
+  ++salt_cpu::g_events_recorded;
+  *reinterpret_cast<int*>(e) = salt_cpu::recording(s) ? -1 : (int)salt_cpu::g_queue.size();
   return hipSuccess;
 }
 inline hipError_t hipEventSynchronize(hipEvent_t e) {
-  return salt_cpu::g_capture.graph || *reinterpret_cast<int*>(e) ? hipErrorCapturedEvent : hipSuccess;
+  const int at = *reinterpret_cast<int*>(e);
+  if (salt_cpu::g_capture.graph || at < 0) return hipErrorCapturedEvent;
+  salt_cpu::run_queue((size_t)at);
+  return hipSuccess;
 }
 inline hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
   const salt_cpu::Alloc* al = salt_cpu::find(p);
@@ -613,14 +635,10 @@ inline hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* 
 template <typename... KArgs, typename... Args>
 inline void hipLaunchKernelGGL(void (*k)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t s,
                                Args&&... args) {
-  if (salt_cpu::recording(s)) {
-    salt_cpu::g_capture.graph->push_back([=] { salt_cpu::launch(grid, block, lds, [&]() { k(args...); }); });
-    return;
-  }
-  salt_cpu::launch(grid, block, lds, [&]() { k(args...); });
+  salt_cpu::enqueue(s, [=] { salt_cpu::launch(grid, block, lds, [&]() { k(args...); }); });
 }
 template <typename... KArgs, typename... Args>
-inline void hipExtLaunchKernelGGL(void (*k)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t, hipEvent_t,
+inline void hipExtLaunchKernelGGL(void (*k)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t s, hipEvent_t,
                                   hipEvent_t, unsigned, Args&&... args) {
-  salt_cpu::launch(grid, block, lds, [&]() { k(args...); });
+  salt_cpu::enqueue(s, [=] { salt_cpu::launch(grid, block, lds, [&]() { k(args...); }); });
 }

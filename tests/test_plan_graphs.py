@@ -1,7 +1,9 @@
 """Graphs of one plan recorded apart from each other: an apply recorded before the
 plan's build is, and builds of batches of several sizes.  A graph keeps the device
 addresses it was recorded with, so a replay must find the maps and the tiles of the
-batch staged last there, whatever was recorded in between.  The maps differ in
+batch staged last there, whatever was recorded in between.  Maps set inside a
+capture likewise, where the first batch of a plan is accepted and any later one
+refused.  The maps differ in
 their group sizes (at equal tile counts, as a graph's launches need).  On the CPU
 build of the runtime and kernels, whose shim records and replays launches
 (tests/cpu_kernels/capture.cpp), and on the GPU; each replay is compared with the
@@ -21,7 +23,10 @@ SKEWS = ((0, 0, 0, 0), (-1, 2, -2, 1), (3, -1, 0, -2))
 
 @pytest.mark.skipif(not cpu_build.available(), reason="needs the ROCm host clang")
 @pytest.mark.parametrize("sequence,T", [("apply_then_build", 16), ("apply_then_build", 200), ("two_sizes", 100),
-                                        ("two_sizes", 5000)])
+                                        ("two_sizes", 5000), ("maps_in_capture", 16), ("maps_in_capture", 200),
+                                        ("maps_in_capture", 5000), ("maps_in_capture_built_outside", 16),
+                                        ("maps_in_capture_built_outside", 200),
+                                        ("maps_in_capture_built_outside", 5000)])
 def test_on_the_cpu(sequence, T):
     r = cpu_build.program("capture", sequence, str(T))
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
@@ -145,5 +150,37 @@ def test_builds_of_two_sizes():
                 g.set(m[k]); g.reset()
                 g.replay(ex)
                 assert np.array_equal(g.result(), w[k]), (len(m[0][0]), k)
+    finally:
+        g.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T", [16, 200, 5000])
+def test_maps_set_inside_a_capture(T):
+    print(f"\n[gpu case] maps set inside a capture, {T} tokens", flush=True)
+    from paper_2608_03579_amd import salt
+    g = Graphs(T)
+    try:
+        maps = g.maps(T)
+        want = g.expected(maps)
+
+        def second():
+            with pytest.raises(salt.SaltError) as e:
+                g.set(maps[1])
+            assert e.value.status == salt.ERR_BAD_STATE
+
+        ex = g.record(lambda: g.set(maps[0]), g.build, g.apply, second)
+        last = 0
+        for k in (None, None, 1, 2, None, 0, 1):
+            if k is not None:
+                g.set(maps[k])
+                last = k
+            g.reset()
+            g.replay(ex)
+            assert np.array_equal(g.result(), want[last]), (k, last)
+        g.record(second)
+        g.set(maps[2]); g.build(); g.reset(); g.apply()
+        assert np.array_equal(g.result(), want[2])
+        assert g.run.plan.errors(g.run.stream) == 0
     finally:
         g.close()
