@@ -19,6 +19,8 @@ struct PlanLaunch {
   const int4* maps;     // [T] staged maps: (c, u, r, gamma bits) by token
   int4* tiles;          // [n_tiles] tile headers (i0, n, c, largest rank), on the device
   const int4* tiles_src;// null, or where the build copies them from (maps + T; up to kSortChunk tokens)
+  uint64_t* read_seq;   // null, or a page-locked host word that receives seq once the maps and tiles were read
+  uint64_t seq;         // (batches of one chunk)
   uint64_t* keys;       // [T] chunk-sorted keys (batches of more than one chunk)
   uint64_t* keys_sorted;// [T] sorted keys (idem)
   int4* srt;            // [T] (token, slot, rank, gamma bits) at each place

@@ -214,6 +214,10 @@ __global__ void __launch_bounds__(NT) k_plan_sort(const PlanLaunch a) {
     s_keys2[0][tid + NT * e] = r[e];
   }
   __syncthreads();
+  // every map and tile is in LDS, in device memory or on its way there: the host may
+  // write the staging buffer again (a number in its memory costs the stream nothing)
+  if (a.read_seq && tid == 0)
+    __hip_atomic_store(a.read_seq, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   int cur = 0;
   int n2 = 64;                               // the merges span the power of two that holds the keys
   while (n2 < cnt) n2 <<= 1;

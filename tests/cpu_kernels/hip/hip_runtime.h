@@ -92,7 +92,8 @@ typedef enum {
   hipErrorInvalidSymbol = 13,
   hipErrorLaunchFailure = 719,
   hipErrorStreamCaptureUnsupported = 900,
-  hipErrorCapturedEvent = 907
+  hipErrorCapturedEvent = 907,
+  hipErrorNotReady = 600
 } hipError_t;
 typedef struct salt_cpu_stream* hipStream_t;
 typedef struct salt_cpu_event* hipEvent_t;
@@ -349,6 +350,8 @@ inline int salt_cpu_update_dpp(int, int v, int ctrl, int, int, bool) {
   return salt_cpu::wave_xchg(v, (l & ~3) | ((ctrl >> (2 * (l & 3))) & 3));
 }
 #define __builtin_amdgcn_update_dpp salt_cpu_update_dpp
+#define __HIP_MEMORY_SCOPE_SYSTEM 0
+#define __hip_atomic_store(p, v, order, scope) __atomic_store_n(p, v, order)
 inline int atomicAdd(int* p, int v) {
   const int o = *p;
   *p = o + v;
@@ -600,6 +603,12 @@ inline hipError_t hipStreamSynchronize(hipStream_t s) {
   if (salt_cpu::forbidden() || salt_cpu::recording(s)) return hipErrorStreamCaptureUnsupported;
   salt_cpu::run_queue(salt_cpu::g_queue.size());
   return hipSuccess;
+}
+inline hipError_t hipStreamQuery(hipStream_t s) {       // (a lazy queue runs a node meanwhile)
+  if (salt_cpu::forbidden() || salt_cpu::recording(s)) return hipErrorStreamCaptureUnsupported;
+  if (salt_cpu::g_ran == salt_cpu::g_queue.size()) return hipSuccess;
+  salt_cpu::run_queue(salt_cpu::g_ran + 1);
+  return hipErrorNotReady;
 }
 inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
 inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {

@@ -3,7 +3,8 @@ plan's build is, and builds of batches of several sizes.  A graph keeps the devi
 addresses it was recorded with, so a replay must find the maps and the tiles of the
 batch staged last there, whatever was recorded in between.  Maps set inside a
 capture likewise, where the first batch of a plan is accepted and any later one
-refused.  The maps differ in
+refused; and batches staged while earlier ones are in flight, with no event between
+a build and its apply.  The maps differ in
 their group sizes (at equal tile counts, as a graph's launches need).  On the CPU
 build of the runtime and kernels, whose shim records and replays launches
 (tests/cpu_kernels/capture.cpp), and on the GPU; each replay is compared with the
@@ -26,7 +27,8 @@ SKEWS = ((0, 0, 0, 0), (-1, 2, -2, 1), (3, -1, 0, -2))
                                         ("two_sizes", 5000), ("maps_in_capture", 16), ("maps_in_capture", 200),
                                         ("maps_in_capture", 5000), ("maps_in_capture_built_outside", 16),
                                         ("maps_in_capture_built_outside", 200),
-                                        ("maps_in_capture_built_outside", 5000)])
+                                        ("maps_in_capture_built_outside", 5000), ("batches_in_flight", 16),
+                                        ("batches_in_flight", 200), ("batches_in_flight", 5000)])
 def test_on_the_cpu(sequence, T):
     r = cpu_build.program("capture", sequence, str(T))
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
