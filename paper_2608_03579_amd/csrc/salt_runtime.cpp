@@ -184,7 +184,7 @@ struct salt_ctx {
   salt::GramTable* gram_tabs = nullptr;  // the tables as salt_adapter_gram's kernels read them, since set-up
   char* gram = nullptr;                  // salt_adapter_gram's device scratch, grown on demand
   size_t gram_bytes = 0;
-  double* gram_out = nullptr;            // its results [n_tables][3], page-locked, written by the device
+  double* gram_out = nullptr;            // its results [n_tables][3], page-locked since set-up, written by the device
   double* gram_out_dev = nullptr;        // the same as the device addresses them
   hipStream_t side = nullptr;
   // bookkeeping
@@ -956,6 +956,16 @@ salt_status salt_create(const salt_config* cfg, salt_ctx** out) {
   e = hipMemcpy(c->zeros, page.data(), page.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) return bail(SALT_ERR_HIP, e, "zero page");
+  // (here and not in the first salt_adapter_gram, which a page-locked allocation would slow down)
+  void* view = nullptr;
+  if (hipHostMalloc((void**)&c->gram_out, sizeof(double) * 3 * c->tables.size(), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    c->gram_out = nullptr;
+    return bail(SALT_ERR_OUT_OF_MEMORY, hipSuccess, "");
+  }
+  e = hipHostGetDevicePointer(&view, c->gram_out, 0);
+  if (e != hipSuccess) return bail(SALT_ERR_HIP, e, "hipHostGetDevicePointer");
+  c->gram_out_dev = static_cast<double*>(view);
   c->slot_stride = round_up(std::max<size_t>(1, salt_residual_bytes(c, cfg->r_u_max)), kAlign);
   if (hipMalloc((void**)&c->pool, c->slot_stride * (size_t)cfg->n_slots) != hipSuccess) {
     (void)hipGetLastError();
@@ -1261,7 +1271,7 @@ salt_status salt_adapter_gram(salt_ctx* ctx, const void* blob1, int32_t r1, cons
     a.chunks = std::max(a.chunks, salt::cdiv(sh.in_dim, a.kc) + salt::cdiv(sh.out_dim, a.kc));
   a.g_table = (per_chunk ? (size_t)a.chunks : 2) * a.g_side;
   // one scratch buffer per context for the Grams, which grows to the largest
-  // call so far, and one page-locked buffer that the device writes the results to
+  // call so far (the results go to a page-locked buffer, there since set-up)
   const size_t need = sizeof(float) * a.g_table * nt;
   if (need > ctx->gram_bytes) {
     // (the previous buffer is idle: every earlier call synchronised its stream)
@@ -1274,16 +1284,6 @@ salt_status salt_adapter_gram(salt_ctx* ctx, const void* blob1, int32_t r1, cons
       return fail(ctx, SALT_ERR_OUT_OF_MEMORY, "adapter Gram scratch (%zu bytes)", need);
     }
     ctx->gram_bytes = need;
-  }
-  if (!ctx->gram_out) {
-    void *p = nullptr, *d = nullptr;
-    if (hipHostMalloc(&p, sizeof(double) * 3 * nt, hipHostMallocDefault) != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(ctx, SALT_ERR_OUT_OF_MEMORY, "adapter Gram results");
-    }
-    ctx->gram_out = static_cast<double*>(p);
-    SALT_HIP(ctx, hipHostGetDevicePointer(&d, p, 0));
-    ctx->gram_out_dev = static_cast<double*>(d);
   }
   a.g = reinterpret_cast<float*>(ctx->gram);
   a.out = ctx->gram_out_dev;

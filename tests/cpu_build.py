@@ -30,7 +30,7 @@ SHIM = os.path.join(HERE, "cpu_kernels")
 BUILD = os.path.join(SHIM, "_build")
 SOURCES = ("salt_plan.hip", "salt_apply.hip", "salt_fuse_gram.hip", "salt_swap.hip", "salt_runtime.cpp")
 HEADERS = ("salt_device.h", "salt_internal.h", "salt_layout.h", "salt_launch.h")
-PROGRAMS = ("capture",)          # tests/cpu_kernels/<name>.cpp
+PROGRAMS = ("capture", "gram")   # tests/cpu_kernels/<name>.cpp
 DYN_LDS = "extern __shared__ __attribute__((aligned(16))) char lds[];"
 CLANG = "/opt/rocm/llvm/bin/clang++"
 

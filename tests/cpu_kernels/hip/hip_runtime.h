@@ -503,7 +503,8 @@ inline Capture g_capture;
 inline bool g_lazy = false;
 inline std::vector<std::function<void()>> g_queue;
 inline size_t g_ran = 0;                        // nodes of g_queue already run
-inline int g_events_recorded = 0;
+inline int g_events_recorded = 0, g_host_mallocs = 0;
+inline size_t g_malloc_limit = ~(size_t)0, g_last_malloc = 0;   // bytes of one hipMalloc: most allowed, last
 inline void run_queue(size_t end) {
   for (; g_ran < end; ++g_ran) g_queue[g_ran]();
 }
@@ -550,6 +551,11 @@ inline hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
 }
 inline hipError_t hipMalloc(void** p, size_t n) {
   if (salt_cpu::forbidden()) return hipErrorStreamCaptureUnsupported;
+  if (n > salt_cpu::g_malloc_limit) {
+    *p = nullptr;
+    return hipErrorOutOfMemory;
+  }
+  salt_cpu::g_last_malloc = n;
   *p = salt_cpu::alloc(n, false);
   return *p ? hipSuccess : hipErrorOutOfMemory;
 }
@@ -559,6 +565,7 @@ inline hipError_t hipMalloc(T** p, size_t n) {
 }
 inline hipError_t hipFree(void* p) { return (!p || salt_cpu::release(p)) ? hipSuccess : hipErrorInvalidValue; }
 inline hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  ++salt_cpu::g_host_mallocs;
   *p = salt_cpu::alloc(n, true);
   return *p ? hipSuccess : hipErrorOutOfMemory;
 }
