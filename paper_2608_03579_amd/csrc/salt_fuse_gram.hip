@@ -174,7 +174,7 @@ __global__ void __launch_bounds__(256) k_gram(GramArgs a) {
   const E* x1 = reinterpret_cast<const E*>(a.blob1) + a.r1 * first;
   const E* x2 = reinterpret_cast<const E*>(a.blob2) + a.r2 * first;
   const int r1 = a.r1, r2 = a.r2, nb1 = (r1 + 15) / 16, nb2 = (r2 + 15) / 16;
-  float* g = a.g + (size_t)t * a.g_table + (size_t)(NB > 0 ? local : side) * a.g_side;
+  float* g = a.g + (size_t)(a.by_side ? 2 * t + side : tab.chunk0 + local) * a.g_side;
   // tiles: [0, nb1 * nb2) of G12, then nb1 * nb1 of G11, then nb2 * nb2 of G22
   const int n12 = nb1 * nb2, n11 = nb1 * nb1, ntile = n12 + n11 + nb2 * nb2;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g8 = lane >> 4;
@@ -288,7 +288,7 @@ __global__ void __launch_bounds__(256) k_gram_finish(GramArgs a) {
   const int t = blockIdx.x;
   const GramTable tab = a.tabs[t];
   const int na = kChunks ? cdiv(tab.in_dim, a.kc) : 1, nb = kChunks ? cdiv(tab.out_dim, a.kc) : 1;
-  const float* gA = a.g + (size_t)t * a.g_table;
+  const float* gA = a.g + (size_t)(a.by_side ? 2 * t : tab.chunk0) * a.g_side;
   const float* gB = gA + (size_t)na * a.g_side;
   const int sizes[3] = {a.g_12, a.g_11, a.g_22};
   const int offs[3] = {0, a.g_12, a.g_12 + a.g_11};

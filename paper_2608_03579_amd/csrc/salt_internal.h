@@ -49,30 +49,32 @@ struct FuseArgs {
 // the Grams X1 X2^T [nb1*16][nb2*16], X1 X1^T [nb1*16][nb1*16], X2 X2^T
 // [nb2*16][nb2*16] (ranks padded to 16) of each table's two factor sides (At: over
 // in, B: over out).  For ranks up to 32 g holds them per (table, K chunk), the
-// in chunks first, each written by one block; above, per table and side, summed
-// with atomics in a cleared g.  out[3 t + 0..2] = Tr(dW1^T dW2), ||dW1||^2, ||dW2||^2.
-struct GramTable {          // a context's tables, on the device since salt_create
+// in chunks first, each written by one block, table after table; above, per table
+// and side, summed with atomics in a cleared g.  out[3 t + 0..2] = Tr(dW1^T dW2), ||dW1||^2, ||dW2||^2.
+struct alignas(32) GramTable {   // (one scalar load) a context's tables, on the device since salt_create
   int64_t prefix;           // sum of (in + out) over the earlier tables
   int32_t in_dim, out_dim;
+  int32_t chunk0;           // per-chunk Grams: chunks of kGramChunk elements of the earlier tables
 };
+constexpr int kGramChunk = 1024;
 struct GramArgs {
   const GramTable* tabs;    // [n_tables], device
   const char* blob1;        // table after table At [r][in], B [r][out]
   const char* blob2;
   int32_t n_tables, r1, r2;
   int32_t kc, chunks;       // K elements of a chunk; chunks a table has at most
+  int32_t by_side;          // g holds one Gram set per table and side (not per chunk of kGramChunk)
   float* g;
-  size_t g_table, g_side;   // floats per table, per chunk or per factor side
+  size_t g_side;            // floats of one set
   int32_t g_12, g_11, g_22; // floats of each Gram
   double* out;              // [n_tables][3], device-visible
 };
-// Whether adapters of ranks r1, r2 take the per-chunk Grams, and their chunk length:
-// per chunk up to rank 32, where a wave holds every tile of a step; 1024 elements
-// split two rank-16 adapters over 196 tables into 1,700 blocks, two rounds of the
-// device.  Above rank 32 per-chunk Grams would grow the scratch with the square
-// of the rank (1.2 GB for rank 256), so those sum with atomics.
+// Whether adapters of ranks r1, r2 take the per-chunk Grams: up to rank 32, where a
+// wave holds every tile of a step.  The scratch is then 3 to 12 KB to a chunk, a
+// fifth of a bf16 rank-32 adapter's own bytes.  Above rank 32 it would grow with the
+// square of the rank, so those sum with atomics, over chunks of kGramChunkWide.
 constexpr bool gram_per_chunk(int r1, int r2) { return r1 <= 32 && r2 <= 32; }
-constexpr int gram_chunk(int r1, int r2) { return gram_per_chunk(r1, r2) ? 1024 : 2048; }
+constexpr int kGramChunkWide = 2048;
 
 // Residual blobs one swap launch gathers from mapped page-locked host memory:
 // blob i is vecs[i] 16-byte vectors from src[i] (a device-visible host address)

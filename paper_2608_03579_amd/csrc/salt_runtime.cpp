@@ -182,6 +182,7 @@ struct salt_ctx {
   size_t slot_stride = 0;
   char* zeros = nullptr;                 // zero page of max(in, out) * esize bytes, never written after set-up
   salt::GramTable* gram_tabs = nullptr;  // the tables as salt_adapter_gram's kernels read them, since set-up
+  int32_t gram_chunks = 0;               // their K chunks of kGramChunk elements
   char* gram = nullptr;                  // salt_adapter_gram's device scratch, grown on demand
   size_t gram_bytes = 0;
   double* gram_out = nullptr;            // its results [n_tables][3], page-locked since set-up, written by the device
@@ -945,8 +946,9 @@ salt_status salt_create(const salt_config* cfg, salt_ctx** out) {
   const size_t rec_bytes = c->tables.size() * sizeof(salt::GramTable);
   std::vector<char> page(zero_bytes + rec_bytes, 0);
   for (size_t t = 0; t < c->tables.size(); ++t) {
-    const salt::GramTable g{c->tab_prefix[t], c->tables[t].in_dim, c->tables[t].out_dim};
+    const salt::GramTable g{c->tab_prefix[t], c->tables[t].in_dim, c->tables[t].out_dim, c->gram_chunks};
     std::memcpy(page.data() + zero_bytes + t * sizeof g, &g, sizeof g);
+    c->gram_chunks += salt::cdiv(g.in_dim, salt::kGramChunk) + salt::cdiv(g.out_dim, salt::kGramChunk);
   }
   if (hipMalloc((void**)&c->zeros, page.size()) != hipSuccess) {
     (void)hipGetLastError();
@@ -1265,15 +1267,14 @@ salt_status salt_adapter_gram(salt_ctx* ctx, const void* blob1, int32_t r1, cons
   a.blob2 = static_cast<const char*>(blob2);
   a.tabs = ctx->gram_tabs;
   const bool per_chunk = salt::gram_per_chunk(r1, r2);
-  a.kc = salt::gram_chunk(r1, r2);
-  a.chunks = 2;
-  for (const salt_shape& sh : ctx->tables)
-    a.chunks = std::max(a.chunks, salt::cdiv(sh.in_dim, a.kc) + salt::cdiv(sh.out_dim, a.kc));
-  a.g_table = (per_chunk ? (size_t)a.chunks : 2) * a.g_side;
+  a.kc = per_chunk ? salt::kGramChunk : salt::kGramChunkWide;
+  a.by_side = !per_chunk;
   // one scratch buffer per context for the Grams, which grows to the largest
   // call so far (the results go to a page-locked buffer, there since set-up)
-  const size_t need = sizeof(float) * a.g_table * nt;
-  if (need > ctx->gram_bytes) {
+  const size_t by_side = sizeof(float) * a.g_side * 2 * nt;
+  size_t need = per_chunk ? sizeof(float) * a.g_side * ctx->gram_chunks : by_side;
+  auto grow = [&]() {
+    if (need <= ctx->gram_bytes) return true;
     // (the previous buffer is idle: every earlier call synchronised its stream)
     if (ctx->gram) (void)hipFree(ctx->gram);
     ctx->gram = nullptr;
@@ -1281,10 +1282,23 @@ salt_status salt_adapter_gram(salt_ctx* ctx, const void* blob1, int32_t r1, cons
     if (hipMalloc((void**)&ctx->gram, need) != hipSuccess) {
       (void)hipGetLastError();
       ctx->gram = nullptr;
-      return fail(ctx, SALT_ERR_OUT_OF_MEMORY, "adapter Gram scratch (%zu bytes)", need);
+      return false;
     }
     ctx->gram_bytes = need;
+    return true;
+  };
+  bool fits = grow();
+  if (!fits && need > by_side) {
+    // no room for every chunk's Grams: one chunk to a side
+    for (const salt_shape& sh : ctx->tables) a.kc = std::max({a.kc, sh.in_dim, sh.out_dim});
+    a.by_side = 1;
+    need = by_side;
+    fits = grow();
   }
+  if (!fits) return fail(ctx, SALT_ERR_OUT_OF_MEMORY, "adapter Gram scratch (%zu bytes)", need);
+  a.chunks = 2;
+  for (const salt_shape& sh : ctx->tables)
+    a.chunks = std::max(a.chunks, salt::cdiv(sh.in_dim, a.kc) + salt::cdiv(sh.out_dim, a.kc));
   a.g = reinterpret_cast<float*>(ctx->gram);
   a.out = ctx->gram_out_dev;
   if (!per_chunk) SALT_HIP(ctx, hipMemsetAsync(a.g, 0, need, s));
