@@ -1168,7 +1168,7 @@ k_expand(const ApplyLaunch a) {
   for (int pos = expand_begin(a, blockIdx.x, gridDim.x); pos < end;) {
     const ExpandSeg sg = expand_seg(a, pos, end);
     __syncthreads();
-    if constexpr (quad_expand(M, RU)) expand_segment_quad<E, M, NB, RU>(a, sg, lds);
+    if constexpr (quad_expand(M, 16 * NB, RU)) expand_segment_quad<E, M, NB, RU>(a, sg, lds);
     else expand_segment<E, M, NB, RU>(a, sg, lds);
     pos += sg.j1 - sg.j0;                                    // (>= 1)
   }
@@ -1197,7 +1197,7 @@ size_t shrink_lds() {
 }
 template <typename E, int M, int NB, int RU>
 size_t expand_lds(int R) {
-  const size_t half = quad_expand(M, RU) ? (size_t)16 * quad_half<M, NB>()
+  const size_t half = quad_expand(M, 16 * NB, RU) ? (size_t)16 * quad_half<M, NB>()
                                          : sizeof(E) * depth<E, M, NB, RU>() * 64 * waves_along<M>() * stage_row_b<NB>();
   const size_t stg = staged<E, M, NB>() ? 2 * half : 0;
   const size_t sv = sizeof(float) * (size_t)M * R;

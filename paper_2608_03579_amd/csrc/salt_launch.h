@@ -188,7 +188,7 @@ inline bool configure_launch(ApplyLaunch& a, int n_cu, int n_groups_c, int64_t s
     poff += (int64_t)jb.S * a.T * a.R;
     // expand: work items of one block-chunk (kChunkCols per wave along the
     // columns); the launch splits them evenly over one round of blocks
-    jb.cpb = (quad_expand(a.M, a.r_u) ? kQuadCols : kChunkCols) * CW;
+    jb.cpb = (quad_expand(a.M, a.r_c, a.r_u) ? kQuadCols : kChunkCols) * CW;
     jb.n_col = cdiv(jb.out, jb.cpb);
     jb.shrink_base = a.shrink_base[j] = sb;
     jb.expand_base = a.expand_base[j] = eb;

@@ -299,7 +299,12 @@ SALT_HD int quad_col(int i, int t) { return 32 * (i >> 2) + 4 * t + (i & 3); }
 // cheaper set-up serve short groups better (Llama-3.1-8B decode T = 256: 34.5 us
 // against 36 us, Zipf T = 512: 35 against 39, 64-token tiles of rank 2: 41 against
 // 49), and so do 128-token tiles of rank 2, for whose second row the quad layout
-// has no registers left (prefill T = 8192, r_c = 64: 266 us against 291 us).
-SALT_HD constexpr bool quad_expand(int M, int r_u) { return (M == 128 && r_u <= 1) || r_u > 2; }
+// has no registers left (prefill T = 8192, r_c = 64: 266 us against 291 us), or of
+// centroid ranks above 64, whose eight fragments leave one block of it to a compute
+// unit (Llama-3.2-3B layer, T = 8192, rank 1: r_c = 72 396 us against 442 in the
+// quad layout, 128 437 against 488; T = 4096: 237 / 255, 267 / 292).
+SALT_HD constexpr bool quad_expand(int M, int r_c, int r_u) {
+  return (M == 128 && r_c <= 64 && r_u <= 1) || r_u > 2;
+}
 
 }  // namespace salt

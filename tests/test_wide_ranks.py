@@ -1,4 +1,4 @@
-"""The apply of residual ranks above 2 and of 128-token tiles (the quad lane layout)
+"""The apply of residual ranks above 2 and of 128-token tiles (in the lane layouts)
 at the sizes where it can go wrong: ranks at the edges of the 16-rank chunks, the
 8-rank passes and the row groups, tiles that hold narrow and wide ranks side by
 side, tokens with and without a centroid, every tile size, centroid ranks that
@@ -23,6 +23,7 @@ CASES = [
     ("m64 ranks 2/3", "bf16", 1, 24, 130, 9, (2, 3), 64),
     ("m64 no centroid ranks 4/33", "bf16", 0, 0, 150, 10, (4, 33), 64),
     ("m128 rank 1", "bf16", 1, 8, 420, 20, (1,), 128),
+    ("m128 rank 1 r_c 72", "bf16", 1, 72, 410, 20, (1,), 128),
     ("m128 ranks 0/2", "bf16", 1, 56, 390, 20, (0, 2), 128),
     ("m128 ranks 1/17", "bf16", 1, 72, 400, 20, (1, 17), 128),
     ("fp32 ranks 1/5/20", "f32", 2, 24, 36, 10, (1, 5, 20), 16),
