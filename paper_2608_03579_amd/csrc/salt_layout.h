@@ -154,12 +154,15 @@ SALT_HD TokRec clamp_tok(const ApplyLaunch& a, int4 rec, bool real) {
 
 // ---- block decomposition ----------------------------------------------------------
 SALT_HD int job_of(const int32_t (&base)[kMaxJobs], int b) {
-  int j = 0;
+  int n = 0;               // (whole-number steps on the scalar unit: base[i] <= b adds one)
 #if defined(__clang__)
 #pragma unroll
 #endif
-  for (int i = 1; i < kMaxJobs; ++i) j += b >= base[i];
-  return j;
+  for (int i = 1; i < kMaxJobs; ++i) n += (int)((uint32_t)(base[i] - 1 - b) >> 31);
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+s"(n));       // (one product with the record's size, not one per step)
+#endif
+  return n;
 }
 SALT_HD int job_of_shrink(const ApplyLaunch& a, int b) { return job_of(a.shrink_base, b); }
 SALT_HD int job_of_expand(const ApplyLaunch& a, int b) {
