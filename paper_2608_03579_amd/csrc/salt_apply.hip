@@ -49,8 +49,8 @@ namespace {
 // into an LDS stage from which each wave reads its MFMA fragments, so the
 // operand is read from L2 once per M tokens.
 //
-// Two lane layouts, row and quad (salt_layout.h); quad_expand says which expands
-// use the latter, and the shrink does for residual ranks above 2.
+// Two lane layouts, row and quad (salt_layout.h); quad_rank1 and quad_rows say which
+// expands use the latter, and wide_shrink which shrinks do.
 template <int M>
 constexpr int waves_along() { return waves_of(M) / (M / 16); }
 template <int M>
@@ -160,7 +160,6 @@ __device__ __forceinline__ void shrink_store(const ApplyLaunch& a, const Job& jb
 template <typename E, int M, int NB, int RU>
 __global__ void __launch_bounds__(threads_of<M>())
 k_shrink(const ApplyLaunch a) {
-  static_assert(RU <= 2, "larger residual ranks run k_shrink_wide");
   using O = Ops<E>;
   using Vec = typename O::Vec;
   constexpr int ES = sizeof(E);
@@ -172,13 +171,14 @@ k_shrink(const ApplyLaunch a) {
   constexpr int PIECES = 16 * NB * 8 * KW;                   // 16-byte pieces of a block-step's A_c slice
   constexpr int NCV = kStage ? (PIECES + NT - 1) / NT : 1;   // staged A_c vectors per thread and block-step
   constexpr int NAC = kStage ? 1 : 2 * NBL;                  // per-lane A_c vectors per step (unstaged)
+  constexpr int RUP = RU <= 2 ? RU : 0;                      // residual ranks in the pipelined operands
   constexpr int U = depth<E, M, NB, RU>();
   extern __shared__ __attribute__((aligned(16))) char lds[];
   float* s_red = reinterpret_cast<float*>(lds);              // [KW][M][WC], after the K loop
   E* s_a = reinterpret_cast<E*>(lds);                        // [2][U][16 NB][SR], during the K loop
 
   const Job& jb = a.jobs[job_of_shrink(a, blockIdx.x)];
-  const ShrinkCoord sc = shrink_coord(a, jb, blockIdx.x);
+  const ShrinkCoord sc = shrink_coord(a, jb, blockIdx.x, RU <= 8);
   const TileHdr th = shrink_tile(a, sc.tau);
   if (th.n <= 0) return;                                     // (no tile is empty; the whole block leaves)
   const int in = jb.in;
@@ -186,7 +186,9 @@ k_shrink(const ApplyLaunch a) {
   const int mb = wave % TB, kq = wave / TB, row = lane & 15, g = lane >> 4;
   const int kt = mb * 16 + row;                              // this lane's token within the tile
   const TokRec tr = clamp_tok(a, a.srt[tile_pos(th, kt)], kt < th.n);
-  const bool has_c = NB > 0 && th.c >= 0;
+  const int r0 = sc.q * kRankChunk;                          // first residual rank of this block
+  if (RU == kRankChunk && sc.q > 0 && r0 >= th.r) return;    // (block-uniform: no token of the tile has a rank there)
+  const bool has_c = NB > 0 && th.c >= 0 && sc.q == 0;
   const int klo = k_lo(jb, sc.s), khi = k_hi(jb, sc.s), nst = k_steps(jb, sc.s);
   const int nbs = cdiv(nst, KW);                             // block-steps
   const int klast = imax(0, in - 8);                         // last whole vector of a row
@@ -196,10 +198,11 @@ k_shrink(const ApplyLaunch a) {
                              has_c ? (uint32_t)((int64_t)a.r_c * in * ES) : 0u);
   const uint32_t xrow = tr.tok ? (uint32_t)tr.t * (uint32_t)(in * ES) : kOob;
   // residual rows of this lane's slot (the zero page where there is none)
-  const char* au[RU];
+  const char* au[RUP > 0 ? RUP : 1];
 #pragma unroll
-  for (int jj = 0; jj < RU; ++jj)
+  for (int jj = 0; jj < RUP; ++jj)
     au[jj] = (tr.res && jj < tr.r) ? a.pool + atu_byte(a, jb, tr.u, tr.r, jj, 0) : a.zeros;
+  const char* au_wide = tr.res ? a.pool + atu_byte(a, jb, tr.u, tr.r, r0, 0) : a.zeros;
 
   f32x4 acc[NBL];
 #pragma unroll
@@ -211,7 +214,7 @@ k_shrink(const ApplyLaunch a) {
   // the per-lane operands of a batch: block-steps j0 .. j0 + U - 1
   struct Ops1 {
     Vec x[U][2];
-    Vec u[U][RU][2];
+    Vec u[U][RUP > 0 ? RUP : 1][2];
     Vec ac[U][NAC];
   };
   // first k of this lane's vectors in block-step j (a step past the K range
@@ -228,7 +231,7 @@ k_shrink(const ApplyLaunch a) {
         B.x[u][h] = O::bload(rx, oob_unless(step_ok && k + 8 <= khi, xrow + (uint32_t)(k * ES)));
       }
 #pragma unroll
-      for (int jj = 0; jj < RU; ++jj)
+      for (int jj = 0; jj < RUP; ++jj)
 #pragma unroll
         for (int h = 0; h < 2; ++h)
           B.u[u][jj][h] = O::load(reinterpret_cast<const E*>(au[jj] + imin(kb + kPiece * h, klast) * ES));
@@ -291,17 +294,48 @@ k_shrink(const ApplyLaunch a) {
         }
       }
 #pragma unroll
-      for (int jj = 0; jj < RU; ++jj)
+      for (int jj = 0; jj < RUP; ++jj)
 #pragma unroll
         for (int h = 0; h < 2; ++h) accu[jj] = O::dot(B.x[u][h], B.u[u][jj][h], accu[jj]);
     }
   };
+  // residual ranks above 2: the step's rows of 8 ranks at a time, read in place, with
+  // no branch in between (a test of the tile's bound there costs more than it
+  // saves: 77 -> 122 us for 1024 tokens of rank 12; batches of ranks up to 8 have a
+  // kernel of one pass, T = 8192 of rank 4: 386 -> 290 us)
+  auto compute_wide = [&](const Ops1& B, int j) {
+    if constexpr (RU > 2) {
+      static_assert(U == 1, "wide residual ranks run one block-step per batch");
+      const int kb = lane_k(j);
+      const int64_t rs = (int64_t)in * ES;
+#pragma unroll
+      for (int j8 = 0; j8 < RU; j8 += 8) {
+        Vec uv[8][2];
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) {
+          const char* base = (tr.res && r0 + j8 + jj < tr.r) ? au_wide + (j8 + jj) * rs : a.zeros;
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            uv[jj][h] = O::load(reinterpret_cast<const E*>(base + imin(kb + kPiece * h, klast) * ES));
+        }
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) accu[j8 + jj] = O::dot(B.x[0][h], uv[jj][h], accu[j8 + jj]);
+        // (without centroids, one pass's rows at a time: with both in flight the
+        // registers pass the edge of an occupancy step, T = 512 of 4 users 33 -> 26 us)
+        if (NB == 0) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+
   Ops1 A;
   if constexpr (ES == 4) {
     // fp32: one set of operands, loaded then used (its vectors are twice as wide)
     for (int j = 0; j < nbs; ++j) {
       load(A, j);
       compute(A, 0);
+      compute_wide(A, j);
     }
   } else {
     Ops1 Bb;
@@ -315,12 +349,14 @@ k_shrink(const ApplyLaunch a) {
       write_stage(1);
       load_stage(j + 2 * U);
       compute(A, 0);
+      compute_wide(A, j);
       if constexpr (kStage) __syncthreads();
       if (j + U >= nbs) break;                               // (block-uniform)
       load(A, j + 2 * U);
       write_stage(0);
       load_stage(j + 3 * U);
       compute(Bb, 1);
+      compute_wide(Bb, j + U);
       if constexpr (kStage) __syncthreads();
     }
   }
@@ -350,8 +386,8 @@ k_shrink(const ApplyLaunch a) {
   shrink_store<M, NB, RU>(a, jb, sc, th, s_red, has_c);
 }
 
-// Residual ranks above 2 (plain LoRA adapters, long-tail concatenated ones): the
-// shrink of a 16-token tile whose tokens bring up to kRankChunk rows of A_u each
+// Residual ranks above 2 where wide_shrink says so (long-tail concatenated adapters,
+// large batches of plain LoRA ones): the shrink of a 16-token tile whose tokens bring up to kRankChunk rows of A_u each
 // in this block's rank chunk.  Bound by the bandwidth of those rows (every row is
 // one user's, read once per tile), so the kernel is laid out for rows in flight:
 //  - the tile header carries its group's largest rank: a block of a chunk past
@@ -524,6 +560,7 @@ __device__ __forceinline__ void expand_segment(const ApplyLaunch& a, const Expan
   constexpr int NT = threads_of<M>();
   constexpr int NCV = kStage ? (128 * CW * NB + NT - 1) / NT : 1;   // staged B_c vectors per thread and block-chunk
   constexpr int NBC = kStage ? 1 : 4 * KSL;                  // per-lane B_c vectors per chunk (unstaged)
+  constexpr int RUP = RU <= 2 ? RU : 0;                      // residual ranks in the pipelined operands
   constexpr int U = depth<E, M, NB, RU>();
   float* s_v = reinterpret_cast<float*>(lds);                // [M][R] v of the tile
 
@@ -542,21 +579,26 @@ __device__ __forceinline__ void expand_segment(const ApplyLaunch& a, const Expan
   const int nch = cdiv(chi - clo, kChunkCols);               // 64-column chunks
   const int nbj = cdiv(nch, CW);                             // block-chunks
   const int olast = imax(0, out - 8);
-  E* s_b = reinterpret_cast<E*>(lds);                        // [2][U][64 CW][SRB], once v is in registers
+  // residual ranks past the first chunk (long-tail adapters) are read from s_v
+  // inside the column loop, so the stage then sits after it; otherwise s_v is
+  // dead once v is in registers and the stage takes its place
+  const bool long_tail = RU == kRankChunk && a.r_u > RU;
+  E* s_b = reinterpret_cast<E*>(lds + (long_tail ? sizeof(float) * (size_t)M * R : 0));   // [2][U][64 CW][SRB]
 
   const Rsrc ry = make_rsrc(jb.y, (uint32_t)((int64_t)a.T * out * ES));
   const Rsrc rb = make_rsrc(has_c ? static_cast<const char*>(jb.bt_c) + (int64_t)th.c * out * a.r_c * ES : nullptr,
                             has_c ? (uint32_t)((int64_t)out * a.r_c * ES) : 0u);
   const uint32_t yrow = tr.tok ? (uint32_t)tr.t * (uint32_t)(out * ES) : kOob;
-  const char* bu[RU];
+  const char* bu[RUP > 0 ? RUP : 1];
 #pragma unroll
-  for (int jj = 0; jj < RU; ++jj)
+  for (int jj = 0; jj < RUP; ++jj)
     bu[jj] = (tr.res && jj < tr.r) ? a.pool + bu_byte(a, jb, tr.u, tr.r, jj, 0) : a.zeros;
+  const char* bu_wide = tr.res ? a.pool + bu_byte(a, jb, tr.u, tr.r, 0, 0) : a.zeros;
 
   // the per-lane operands of a batch: block-chunks j0 .. j0 + U - 1
   struct Ops1 {
     Vec y[U][2];
-    Vec u[U][RU][2];
+    Vec u[U][RUP > 0 ? RUP : 1][2];
     Vec bc[U][NBC];
   };
   // this lane's first column in block-chunk j
@@ -572,7 +614,7 @@ __device__ __forceinline__ void expand_segment(const ApplyLaunch& a, const Expan
 #pragma unroll
       for (int h = 0; h < 2; ++h) B.y[u][h] = O::bload(ry, y_off(j, h));
 #pragma unroll
-      for (int jj = 0; jj < RU; ++jj)
+      for (int jj = 0; jj < RUP; ++jj)
 #pragma unroll
         for (int h = 0; h < 2; ++h)
           B.u[u][jj][h] = O::load(reinterpret_cast<const E*>(bu[jj] + imin(cl + kPiece * h, olast) * ES));
@@ -759,7 +801,7 @@ __device__ __forceinline__ void expand_segment(const ApplyLaunch& a, const Expan
 #pragma unroll
       for (int e = 0; e < 4; ++e) yf[4 * b4 + e] += d[b4][e];
 #pragma unroll
-    for (int jj = 0; jj < RU; ++jj)
+    for (int jj = 0; jj < RUP; ++jj)
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         float b[8];
@@ -767,6 +809,53 @@ __device__ __forceinline__ void expand_segment(const ApplyLaunch& a, const Expan
 #pragma unroll
         for (int e = 0; e < 8; ++e) yf[8 * h + e] = fmaf(vu[jj], b[e], yf[8 * h + e]);
       }
+    if constexpr (RU > 2) {
+      // residual ranks above 2: this chunk's columns of 8 ranks at a time, read in
+      // place so that eight rows' loads are in flight together, up to the tile's
+      // bound; a lane past its own rank reads the zero page with a zero v
+      const int cl = lane_col(j);
+      const int64_t rs = (int64_t)out * ES;
+      auto rows8 = [&](int r8, const float (&v)[8]) {
+        Vec bv[8][2];
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) {
+          const char* base = (tr.res && r8 + jj < tr.r) ? bu_wide + (r8 + jj) * rs : a.zeros;
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            bv[jj][h] = O::load(reinterpret_cast<const E*>(base + imin(cl + kPiece * h, olast) * ES));
+        }
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            float b[8];
+            O::to_f32(bv[jj][h], b);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) yf[8 * h + e] = fmaf(v[jj], b[e], yf[8 * h + e]);
+          }
+      };
+      float v0[8], v8[8];
+#pragma unroll
+      for (int jj = 0; jj < 8; ++jj) {
+        v0[jj] = vu[jj];
+        v8[jj] = vu[8 + jj];
+      }
+      if (th.r <= 8) {                                       // (block-uniform; no branch between the passes)
+        rows8(0, v0);
+      } else {
+        rows8(0, v0);
+        rows8(8, v8);
+      }
+      if (long_tail) {
+        // ranks past the first chunk, their v from s_v
+        for (int r8 = RU; r8 < th.r; r8 += 8) {
+          float v[8];
+#pragma unroll
+          for (int jj = 0; jj < 8; ++jj) v[jj] = (tr.res && r8 + jj < tr.r) ? vrow[a.r_c + r8 + jj] : 0.f;
+          rows8(r8, v);
+        }
+      }
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) O::bstore(ry, y_off(j, h), yf + 8 * h);
   };
@@ -1160,7 +1249,7 @@ __device__ __forceinline__ void expand_segment_quad(const ApplyLaunch& a, const 
 // items segment by segment (a segment: the block-chunks of one tile).  Every
 // segment starts behind a block barrier, so its LDS writes never meet the
 // previous segment's reads.
-template <typename E, int M, int NB, int RU>
+template <typename E, int M, int NB, int RU, bool Q>
 __global__ void __launch_bounds__(threads_of<M>()) __attribute__((amdgpu_waves_per_eu(expand_waves<E, M, NB, RU>(), 8)))
 k_expand(const ApplyLaunch a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -1168,7 +1257,7 @@ k_expand(const ApplyLaunch a) {
   for (int pos = expand_begin(a, blockIdx.x, gridDim.x); pos < end;) {
     const ExpandSeg sg = expand_seg(a, pos, end);
     __syncthreads();
-    if constexpr (quad_expand(M, 16 * NB, RU)) expand_segment_quad<E, M, NB, RU>(a, sg, lds);
+    if constexpr (Q) expand_segment_quad<E, M, NB, RU>(a, sg, lds);
     else expand_segment<E, M, NB, RU>(a, sg, lds);
     pos += sg.j1 - sg.j0;                                    // (>= 1)
   }
@@ -1185,24 +1274,19 @@ void launch_k(K kernel, int blocks, int threads, size_t lds, hipStream_t s, cons
 }
 
 template <typename E, int M, int NB, int RU>
-constexpr auto shrink_kernel() {
-  if constexpr (RU > 2) return k_shrink_wide<E, NB>;
-  else return k_shrink<E, M, NB, RU>;
-}
-template <typename E, int M, int NB, int RU>
 size_t shrink_lds() {
   const size_t red = sizeof(float) * (size_t)waves_along<M>() * M * shrink_wc<NB, RU>();
   const size_t stg = staged<E, M, NB>() ? sizeof(E) * 2 * depth<E, M, NB, RU>() * 16 * NB * stage_row_a<M>() : 0;
   return red > stg ? red : stg;
 }
-template <typename E, int M, int NB, int RU>
-size_t expand_lds(int R) {
-  const size_t half = quad_expand(M, 16 * NB, RU) ? (size_t)16 * quad_half<M, NB>()
-                                         : sizeof(E) * depth<E, M, NB, RU>() * 64 * waves_along<M>() * stage_row_b<NB>();
+template <typename E, int M, int NB, int RU, bool Q>
+size_t expand_lds(int R, int r_u) {
+  const size_t half = Q ? (size_t)16 * quad_half<M, NB>()
+                        : sizeof(E) * depth<E, M, NB, RU>() * 64 * waves_along<M>() * stage_row_b<NB>();
   const size_t stg = staged<E, M, NB>() ? 2 * half : 0;
   const size_t sv = sizeof(float) * (size_t)M * R;
-  // the stage takes the place of v unless wide ranks read v in the column loop
-  return RU > 2 ? sv + stg : std::max(sv, stg);
+  // the stage takes the place of v unless the column loop reads v
+  return RU > 2 && (Q || r_u > RU) ? sv + stg : std::max(sv, stg);
 }
 
 // Blocks of `kernel` with `lds` bytes of LDS that one compute unit holds at once
@@ -1224,24 +1308,40 @@ int resident_blocks(int threads, size_t lds) {
   return n;
 }
 
-template <typename E, int M, int NB, int RU>
-hipError_t launch_mnr(const ApplyLaunch& a, hipStream_t s, hipEvent_t* ev) {
+template <typename E, int M, int NB, int RU, bool Q>
+hipError_t launch_expand(const ApplyLaunch& a, hipStream_t s, hipEvent_t* ev) {
   constexpr int NT = threads_of<M>();
-  constexpr int MS = RU > 2 ? 16 : (M > 64 ? 64 : M);         // tokens per shrink tile (shrink_tile_tokens)
-  if (a.MS != MS) return hipErrorInvalidValue;
-  launch_k(shrink_kernel<E, MS, NB, RU>(), a.shrink_blocks, threads_of<MS>(), shrink_lds<E, MS, NB, RU>(), s, a,
-           ev ? ev[0] : nullptr, ev ? ev[1] : nullptr);
-  const size_t lds = expand_lds<E, M, NB, RU>(a.R);
-  const int round = resident_blocks<k_expand<E, M, NB, RU>>(NT, lds) * std::max(1, a.n_cu);
+  const size_t lds = expand_lds<E, M, NB, RU, Q>(a.R, a.r_u);
+  const int round = resident_blocks<k_expand<E, M, NB, RU, Q>>(NT, lds) * std::max(1, a.n_cu);
   // One round of blocks walks the items, an equal share each.  Where some tiles
   // hold ranks of several chunks an item costs as much as its tokens' ranks, and
   // equal shares would leave most of the device idle behind the blocks that got
   // the long ones (Zipf T = 512 with rank-65/66 users: 268 us): eight rounds,
   // handed out as blocks finish (143 us).
-  const int rounds = RU > 2 && a.n_pairs > a.n_stiles ? 8 : 1;
+  const int rounds = RU > 2 && a.uneven ? 8 : 1;
   const int grid = (int)std::min<int64_t>(a.expand_items, (int64_t)rounds * round);
-  launch_k(k_expand<E, M, NB, RU>, grid, NT, lds, s, a, ev ? ev[2] : nullptr, ev ? ev[3] : nullptr);
+  launch_k(k_expand<E, M, NB, RU, Q>, grid, NT, lds, s, a, ev ? ev[2] : nullptr, ev ? ev[3] : nullptr);
   return hipGetLastError();
+}
+
+template <typename E, int M, int NB, int RU>
+hipError_t launch_mnr(const ApplyLaunch& a, hipStream_t s, hipEvent_t* ev) {
+  constexpr int MS = M > 64 ? 64 : M;                         // tokens per shrink tile of the row layout
+  hipEvent_t e0 = ev ? ev[0] : nullptr, e1 = ev ? ev[1] : nullptr;
+  if (a.MS != (a.wide ? 16 : MS) || (a.wide && RU <= 2)) return hipErrorInvalidValue;
+  if (RU > 2 && a.wide)
+    launch_k(k_shrink_wide<E, NB>, a.shrink_blocks, threads_of<16>(), shrink_lds<E, 16, NB, kRankChunk>(), s, a, e0, e1);
+  else if (RU > 2 && a.r_u <= 8)
+    launch_k(k_shrink<E, MS, NB, 8>, a.shrink_blocks, threads_of<MS>(), shrink_lds<E, MS, NB, 8>(), s, a, e0, e1);
+  else
+    launch_k(k_shrink<E, MS, NB, RU>, a.shrink_blocks, threads_of<MS>(), shrink_lds<E, MS, NB, RU>(), s, a, e0, e1);
+  if constexpr (RU > 2) {
+    return a.quad ? launch_expand<E, M, NB, RU, true>(a, s, ev) : launch_expand<E, M, NB, RU, false>(a, s, ev);
+  } else {
+    constexpr bool Q = quad_rank1(M, 16 * NB, RU);
+    if (a.quad != Q) return hipErrorInvalidValue;
+    return launch_expand<E, M, NB, RU, Q>(a, s, ev);
+  }
 }
 
 template <typename E, int M, int NB>
@@ -1264,16 +1364,14 @@ hipError_t launch_m(const ApplyLaunch& a, hipStream_t s, hipEvent_t* ev) {
 template <typename E, int MS>
 int shrink_round_m(const ApplyLaunch& a) {
   const int nb = centroid_blocks(a.r_c);
-  const int ru = a.r_u <= 1 ? 1 : (a.r_u <= 2 ? 2 : kRankChunk);
+  const int ru = a.r_u <= 1 ? 1 : (a.r_u <= 2 ? 2 : (a.r_u <= 8 ? 8 : kRankChunk));
 #define SALT_ROUND(NB_, RU_) \
-  if (nb == NB_ && ru == RU_) return resident_blocks<shrink_kernel<E, MS, NB_, RU_>()>(threads_of<MS>(), shrink_lds<E, MS, NB_, RU_>()) * std::max(1, a.n_cu);
-  SALT_ROUND(0, 1) SALT_ROUND(0, 2)
-  SALT_ROUND(2, 1) SALT_ROUND(2, 2)
-  SALT_ROUND(4, 1) SALT_ROUND(4, 2)
-  SALT_ROUND(8, 1) SALT_ROUND(8, 2)
-  if constexpr (MS == 16) {
-    SALT_ROUND(0, kRankChunk) SALT_ROUND(2, kRankChunk) SALT_ROUND(4, kRankChunk) SALT_ROUND(8, kRankChunk)
-  }
+  if (nb == NB_ && ru == RU_)  \
+    return resident_blocks<k_shrink<E, MS, NB_, RU_>>(threads_of<MS>(), shrink_lds<E, MS, NB_, RU_>()) * std::max(1, a.n_cu);
+  SALT_ROUND(0, 1) SALT_ROUND(0, 2) SALT_ROUND(0, 8) SALT_ROUND(0, kRankChunk)
+  SALT_ROUND(2, 1) SALT_ROUND(2, 2) SALT_ROUND(2, 8) SALT_ROUND(2, kRankChunk)
+  SALT_ROUND(4, 1) SALT_ROUND(4, 2) SALT_ROUND(4, 8) SALT_ROUND(4, kRankChunk)
+  SALT_ROUND(8, 1) SALT_ROUND(8, 2) SALT_ROUND(8, 8) SALT_ROUND(8, kRankChunk)
 #undef SALT_ROUND
   return 0;
 }
@@ -1281,7 +1379,7 @@ int shrink_round_m(const ApplyLaunch& a) {
 }  // namespace
 
 int shrink_round_blocks(const ApplyLaunch& a) {
-  if (a.esize == 4) return shrink_round_m<float, 16>(a);
+  if (a.esize == 4 || a.wide) return 0;                       // (asked for tiles of 64 tokens only)
   switch (a.MS) {
     case 16: return shrink_round_m<uint16_t, 16>(a);
     case 32: return shrink_round_m<uint16_t, 32>(a);
@@ -1334,14 +1432,17 @@ hipError_t kernels_init(int device) {
   hipError_t e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, device);
   if (e != hipSuccess) return e;
   const int R = padded_rank(kMaxRc, kMaxRu);
-  const size_t need_expand = std::max({expand_lds<uint16_t, 64, 8, kRankChunk>(R),
-                                       expand_lds<uint16_t, 32, 8, kRankChunk>(R),
-                                       expand_lds<uint16_t, 128, 8, kRankChunk>(R),
-                                       expand_lds<uint16_t, 128, 4, 2>(padded_rank(64, 2)),
-                                       expand_lds<uint16_t, 64, 4, 2>(padded_rank(64, 2)),
-                                       expand_lds<uint16_t, 32, 4, 2>(padded_rank(64, 2))});
-  const size_t need_shrink = std::max({shrink_lds<uint16_t, 16, 8, kRankChunk>(), shrink_lds<uint16_t, 64, 8, 2>(),
-                                       shrink_lds<uint16_t, 32, 8, 2>(), shrink_lds<uint16_t, 64, 4, 2>(),
+  const size_t need_expand = std::max({expand_lds<uint16_t, 64, 8, kRankChunk, true>(R, kMaxRu),
+                                       expand_lds<uint16_t, 32, 8, kRankChunk, true>(R, kMaxRu),
+                                       expand_lds<uint16_t, 128, 8, kRankChunk, true>(R, kMaxRu),
+                                       expand_lds<uint16_t, 64, 8, kRankChunk, false>(R, kMaxRu),
+                                       expand_lds<uint16_t, 32, 8, kRankChunk, false>(R, kMaxRu),
+                                       expand_lds<uint16_t, 128, 8, kRankChunk, false>(R, kMaxRu),
+                                       expand_lds<uint16_t, 128, 4, 2, false>(padded_rank(64, 2), 2),
+                                       expand_lds<uint16_t, 64, 4, 2, false>(padded_rank(64, 2), 2),
+                                       expand_lds<uint16_t, 32, 4, 2, false>(padded_rank(64, 2), 2)});
+  const size_t need_shrink = std::max({shrink_lds<uint16_t, 16, 8, kRankChunk>(), shrink_lds<uint16_t, 64, 8, kRankChunk>(),
+                                       shrink_lds<uint16_t, 32, 8, kRankChunk>(), shrink_lds<uint16_t, 64, 4, 2>(),
                                        shrink_lds<uint16_t, 32, 4, 2>()});
   const size_t need_plan = (2 * sizeof(uint64_t) + sizeof(int) + 1) * kSortChunk + 256;
   const size_t need = std::max(need_expand, std::max(need_shrink, need_plan));

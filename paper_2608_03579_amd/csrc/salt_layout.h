@@ -11,6 +11,7 @@
 // allocation it belongs to, whatever it holds.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 // SALT_HOST_ONLY: a plain C++ build (no HIP headers) for host-side checks.
@@ -82,39 +83,47 @@ struct Job {
 };
 
 struct ApplyLaunch {
-  // A block's first reads, in one line each: the first shrink block and expand
-  // work item of each job (INT32_MAX past the last job).  A shrink block finds
-  // its job with one scalar load instead of one per job in turn (a decode layer
-  // of four tokens: 6.2 -> 5.3 us); the expand walks its line, since comparing
-  // with all of it costs its column loop the scalar registers (Zipf T = 512: + 1 us).
+  // A block's first reads stand in lines of their own (64 bytes).
+  // The first shrink block and expand work item of each job (INT32_MAX past the last
+  // job), a line each.  A shrink block finds its job with one scalar load instead of
+  // one per job in turn (a decode layer of four tokens: 6.2 -> 5.3 us); the expand
+  // walks its line, since comparing with all of it costs its column loop the scalar
+  // registers (Zipf T = 512: + 1 us).
   int32_t shrink_base[kMaxJobs];
-  int32_t expand_base[kMaxJobs];
-  Job jobs[kMaxJobs];
+  // what every block reads of the batch, two lines
   const int4* tiles;       // [n_tiles]
+  const int4* stiles;      // [n_stiles] the shrink's tiles
   const int4* srt;         // [T] token records in sorted order
   const char* pool;        // residual slot pool
   float* partials;         // split-K partial sums
   const char* zeros;       // zero page: >= max(in, out) * esize bytes of zeros (read in place of missing residual rows)
   int64_t slot_stride;     // bytes between slots
-  int64_t partial_cap;     // floats of `partials`
-  int32_t n_jobs;
   int32_t T;
+  int32_t n_jobs;
   int32_t n_tiles;
-  const int4* stiles;      // [n_stiles] the shrink's tiles (the expand's tiles unless those exceed 64 tokens)
   int32_t n_stiles;
-  int32_t MS;              // tokens per shrink tile (shrink_tile_tokens)
-  int32_t n_pairs;         // (shrink tile, residual rank chunk) pairs that hold a rank, or 0: n_stiles * nq
-  int32_t M;               // tokens per tile (16, 32 or 64)
+  int32_t MS;              // tokens per shrink tile: 16 with `wide`, else min(M, 64)
+  int32_t M;               // tokens per tile (16, 32, 64 or 128)
   int32_t C, r_c;
   int32_t n_slots;
   int32_t r_u;             // largest residual rank of the batch (<= kMaxRu)
   int32_t nq;              // residual rank chunks: ceil(r_u / kRankChunk), >= 1
   int32_t R;               // partial row stride, padded_rank(r_c, r_u)
-  int32_t esize;           // bytes per element (2: bf16, 4: fp32)
-  int32_t shrink_blocks;
   int32_t expand_items;    // expand work items: sum over jobs of n_tiles x n_col
+  int32_t shrink_blocks;
+  // what only the host reads
+  int32_t wide;            // residual ranks above 2: the shrink is k_shrink_wide's (wide_shrink)
+  int32_t quad;            // the expand's lane layout is the quad one
+  int32_t uneven;          // some tiles hold ranks of several chunks, others of fewer
+  int32_t n_pairs;         // (shrink tile, residual rank chunk) pairs that hold a rank, or 0: n_stiles * nq
+  int32_t expand_base[kMaxJobs];
+  Job jobs[kMaxJobs];
+  int64_t partial_cap;     // floats of `partials`
+  int32_t esize;           // bytes per element (2: bf16, 4: fp32)
   int32_t n_cu;            // compute units of the device (sizes the expand grid)
 };
+static_assert(offsetof(ApplyLaunch, tiles) == 64 && offsetof(ApplyLaunch, n_tiles) == 128 &&
+              offsetof(ApplyLaunch, expand_base) == 192 && offsetof(ApplyLaunch, jobs) == 256);
 
 struct TileHdr {
   int i0, n, c;
@@ -172,16 +181,22 @@ SALT_HD int job_of_expand(const ApplyLaunch& a, int b) {
 }
 
 // Shrink item i of job j: shrink tile tau, K range s, residual rank chunk q
-// (items of a job: (q, s, tau) with tau fastest).
+// (items of a job: (q, s, tau) with tau fastest).  one: there is one rank chunk
+// only, and neither of the divisions by S is needed.
 struct ShrinkCoord {
   int tau, s, q;
 };
 SALT_HD int shrink_tiles(const ApplyLaunch& a) { return a.n_stiles; }
-SALT_HD ShrinkCoord shrink_coord(const ApplyLaunch& a, const Job& jb, int item) {
+SALT_HD ShrinkCoord shrink_coord(const ApplyLaunch& a, const Job& jb, int item, bool one = false) {
   const int local = item - jb.shrink_base, nt = imax(shrink_tiles(a), 1);
   ShrinkCoord c;
   c.tau = local % nt;
   const int rest = local / nt;
+  if (one) {
+    c.s = iclamp(rest, 0, jb.S - 1);
+    c.q = 0;
+    return c;
+  }
   c.s = rest % jb.S;
   c.q = iclamp(rest / jb.S, 0, a.nq - 1);
   return c;
@@ -296,8 +311,8 @@ SALT_HD int quad_elem(int lane) { return 32 * (lane >> 4) + 8 * (lane & 3); }
 // of every tile, holds of tiles 2 s and 2 s + 1 the columns 32 g + 8 s + 0..7.
 SALT_HD int quad_col(int i, int t) { return 32 * (i >> 2) + 4 * t + (i & 3); }
 
-// Whether the expand runs in the quad layout: 128-token tiles of ranks up to 1 and
-// residual ranks above 2, whose time is the streams of rows themselves.  Smaller
+// Whether the expand of ranks up to 2 runs in the quad layout: 128-token tiles of
+// ranks up to 1 (for ranks above 2 see quad_rows).  Smaller
 // tiles keep the row layout, whose shorter chunks, two sets of operands and
 // cheaper set-up serve short groups better (Llama-3.1-8B decode T = 256: 34.5 us
 // against 36 us, Zipf T = 512: 35 against 39, 64-token tiles of rank 2: 41 against
@@ -306,8 +321,6 @@ SALT_HD int quad_col(int i, int t) { return 32 * (i >> 2) + 4 * t + (i & 3); }
 // centroid ranks above 64, whose eight fragments leave one block of it to a compute
 // unit (Llama-3.2-3B layer, T = 8192, rank 1: r_c = 72 396 us against 442 in the
 // quad layout, 128 437 against 488; T = 4096: 237 / 255, 267 / 292).
-SALT_HD constexpr bool quad_expand(int M, int r_c, int r_u) {
-  return (M == 128 && r_c <= 64 && r_u <= 1) || r_u > 2;
-}
+SALT_HD constexpr bool quad_rank1(int M, int r_c, int r_u) { return M == 128 && r_c <= 64 && r_u <= 1; }
 
 }  // namespace salt

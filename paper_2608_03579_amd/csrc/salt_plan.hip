@@ -128,7 +128,8 @@ __device__ void plan_finish(const PlanLaunch& a, const uint64_t* keys, const int
   for (int tau = tid; tau < a.n_tiles; tau += NT) {
     const int4 h = tiles[tau];
     const int i0 = iclamp(h.x, 0, T - 1), n = iclamp(h.y, 0, T - i0);
-    const bool first = tau == 0 || tau == a.n_list0, last = tau == a.n_tiles - 1 || tau == a.n_list0 - 1;
+    const bool first = tau == 0 || tau == a.n_list0 || tau == a.n_list1;
+    const bool last = tau == a.n_tiles - 1 || tau == a.n_list0 - 1 || tau == a.n_list1 - 1;
     int start = 0;
     if (!first) {
       const int4 g = tiles[tau - 1];

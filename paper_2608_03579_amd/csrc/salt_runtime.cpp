@@ -139,11 +139,7 @@ struct salt_plan {
   // the batch
   int32_t T = -1;                   // -1: no maps set
   bool built = false;
-  int32_t M = 16;                   // tokens per tile
-  int32_t n_tiles = 0;
-  int32_t MS = 16;                  // tokens per shrink tile
-  int32_t n_stiles = 0;             // shrink tiles: 0 when they are the tiles themselves
-  int32_t n_pairs = 0;              // (shrink tile, residual rank chunk) pairs that hold a rank
+  salt::BatchTiles tiles;
   int32_t n_groups_c = 0;           // centroids referenced
   int32_t ru_max = 0;               // largest residual rank referenced
   int64_t sum_rank = 0;             // ranks summed over the distinct referenced slots
@@ -422,7 +418,7 @@ hipError_t wait_build_read(salt_plan* plan, int stage) {
 
 // The staged batch to where its builds read it from, on `s`.
 hipError_t copy_staged(salt_plan* plan, int4* dst, hipStream_t s) {
-  const size_t n = (size_t)plan->T + plan->n_tiles + plan->n_stiles;
+  const size_t n = (size_t)plan->T + plan->tiles.total();
   return hipMemcpyAsync(dst, plan->staging + (size_t)plan->stage * plan->stage_len, n * sizeof(int4),
                         hipMemcpyHostToDevice, s);
 }
@@ -525,26 +521,19 @@ salt_status set_maps_impl(salt_ctx* ctx, salt_plan* plan, int32_t T, const int32
       ++n_groups;
       n_groups_c += (g > 0);
     }
-  plan->M = salt::choose_tile_tokens((int)ctx->esize, T, n_groups, n_groups_c > 0);
-  // where the shrink's tiles differ (shrink_tile_tokens), the expand's tiles
-  // serve the expand only and the shrink runs its own of the same sorted order
-  std::vector<int4> tiles, stiles;
-  salt::cut_tiles(per_c, plan->M, tiles, &rank_c);
-  plan->MS = salt::shrink_tile_tokens(plan->M, ru_max);
-  if (plan->MS != plan->M) salt::cut_tiles(per_c, plan->MS, stiles, &rank_c);
-  plan->n_pairs = 0;
-  for (const int4& t : plan->MS != plan->M ? stiles : tiles) plan->n_pairs += std::max(1, salt::cdiv(t.w, salt::kRankChunk));
-  if ((int)tiles.size() > plan->tile_cap || (int)stiles.size() > plan->tile_cap)
-    return fail(ctx, SALT_ERR_BAD_STATE, "%zu tiles exceed the plan's %d", std::max(tiles.size(), stiles.size()),
-                plan->tile_cap);
+  // the expand's tiles, and where they differ the shrinks' own of the same order
+  std::vector<int4> tiles;
+  salt::BatchTiles bt =
+      salt::cut_batch(per_c, rank_c, salt::choose_tile_tokens((int)ctx->esize, T, n_groups, n_groups_c > 0), ru_max, tiles);
+  bt.n_slots = (int)slots.size();
+  if ((int)tiles.size() > 2 * plan->tile_cap)
+    return fail(ctx, SALT_ERR_BAD_STATE, "%zu tiles exceed the plan's %d", tiles.size(), 2 * plan->tile_cap);
   std::copy(tiles.begin(), tiles.end(), staging + T);
-  std::copy(stiles.begin(), stiles.end(), staging + T + tiles.size());
   plan->stage = stage;
-  plan->in_args = !plan->captured && T <= salt::kArgTokens && T + (int)(tiles.size() + stiles.size()) <= salt::kArgEntries;
+  plan->in_args = !plan->captured && T <= salt::kArgTokens && T + (int)tiles.size() <= salt::kArgEntries;
   plan->in_place = !plan->captured && !plan->in_args && T <= salt::kInPlaceTokens;
   plan->fixed = plan->captured && T <= salt::kInPlaceTokens;
-  plan->n_tiles = (int32_t)tiles.size();
-  plan->n_stiles = (int32_t)stiles.size();
+  plan->tiles = bt;
   plan->n_groups_c = n_groups_c;
   plan->ru_max = ru_max;
   plan->sum_rank = sum_rank;
@@ -584,8 +573,9 @@ salt_status build_impl(salt_ctx* ctx, salt_plan* plan, hipStream_t s) {
     pl.grp_off = plan->grp_off();
     pl.meta = plan->meta;
     pl.T = plan->T;
-    pl.n_tiles = plan->n_tiles + plan->n_stiles;              // both lists, checked alike
-    pl.n_list0 = plan->n_tiles;
+    pl.n_tiles = plan->tiles.total();                         // every list, checked alike
+    pl.n_list0 = plan->tiles.n_tiles;
+    pl.n_list1 = plan->tiles.n_tiles + plan->tiles.n_rtiles;
     salt::PlanArgs args;
     if (plan->in_args)
       std::copy_n(plan->staging + (size_t)plan->stage * plan->stage_len, pl.T + pl.n_tiles, args.e);
@@ -648,10 +638,6 @@ salt_status apply_impl(salt_ctx* ctx, int32_t n, const int32_t* tables, salt_pla
     const int nj = std::min(salt::kMaxJobs, n - first);
     salt::ApplyLaunch a{};
     a.tiles = plan->staged_dev + T;
-    a.stiles = plan->n_stiles ? plan->staged_dev + T + plan->n_tiles : a.tiles;
-    a.n_stiles = plan->n_stiles ? plan->n_stiles : plan->n_tiles;
-    a.MS = plan->MS;
-    a.n_pairs = plan->n_pairs;
     a.srt = plan->srt;
     a.pool = ctx->pool;
     a.partials = partials;
@@ -660,8 +646,6 @@ salt_status apply_impl(salt_ctx* ctx, int32_t n, const int32_t* tables, salt_pla
     a.partial_cap = partial_cap;
     a.n_jobs = nj;
     a.T = T;
-    a.n_tiles = plan->n_tiles;
-    a.M = plan->M;
     a.C = C;
     a.r_c = ctx->cfg.r_c;
     a.n_slots = ctx->cfg.n_slots;
@@ -682,6 +666,7 @@ salt_status apply_impl(salt_ctx* ctx, int32_t n, const int32_t* tables, salt_pla
       jb.in = sh.in_dim;
       jb.out = sh.out_dim;
     }
+    salt::choose_layouts(a, plan->tiles, plan->sum_rank);
     if (!salt::configure_launch(a, ctx->n_cu, plan->n_groups_c, plan->sum_rank, salt::shrink_round_blocks(a))) {
       if (scratch)
         return fail(ctx, SALT_ERR_OUT_OF_RANGE,
@@ -1084,8 +1069,8 @@ salt_status salt_plan_tiling(salt_ctx* ctx, const salt_plan* plan, int32_t* tile
                              int32_t* launches) {
   if (!ctx || !plan) return SALT_ERR_INVALID_ARG;
   if (plan->T < 0) return fail(ctx, SALT_ERR_BAD_STATE, "no maps were set on the plan");
-  if (tile_tokens) *tile_tokens = plan->M;
-  if (n_tiles) *n_tiles = plan->n_tiles;
+  if (tile_tokens) *tile_tokens = plan->tiles.M;
+  if (n_tiles) *n_tiles = plan->tiles.n_tiles;
   if (launches) *launches = plan->T > 0 ? 2 : 0;
   return SALT_OK;
 }
@@ -1103,10 +1088,10 @@ salt_status salt_plan_errors(salt_ctx* ctx, const salt_plan* plan_c, void* strea
   int32_t meta[salt::kMetaWords];
   SALT_HIP(ctx, hipMemcpy(meta, plan->meta, sizeof meta, hipMemcpyDeviceToHost));
   *n_errors = meta[salt::kMetaErr];
-  if (meta[salt::kMetaNTiles] != plan->n_tiles + plan->n_stiles || meta[salt::kMetaT] != plan->T) {
+  if (meta[salt::kMetaNTiles] != plan->tiles.total() || meta[salt::kMetaT] != plan->T) {
     *n_errors += 1;
     return fail(ctx, SALT_ERR_BAD_STATE, "device plan has %d tiles of %d tokens, host staged %d of %d",
-                meta[salt::kMetaNTiles], meta[salt::kMetaT], plan->n_tiles + plan->n_stiles, plan->T);
+                meta[salt::kMetaNTiles], meta[salt::kMetaT], plan->tiles.total(), plan->T);
   }
   return SALT_OK;
 }

@@ -3,9 +3,11 @@ CPU against ``tests/cpu_kernels/hip``), run under AddressSanitizer.
 
 ``build()`` compiles the sources with the host clang of ROCm, once per source
 hash, into ``tests/cpu_kernels/_build/harness`` (and, beside it, the programs of
-PROGRAMS, which drive the same library through their own sequences).  The only change made to a
-source is the declaration of the dynamic LDS array, which becomes a pointer to
-the exact-size buffer the host runtime allocates for each launch.  ``run()``
+PROGRAMS, which drive the same library through their own sequences).  Two changes are made to the
+sources: the declaration of the dynamic LDS array becomes a pointer to the
+exact-size buffer the host runtime allocates for each launch, and the unit of the
+work by which an apply's layouts are chosen is a hundredth, so that small batches
+run in every layout.  ``run()``
 writes a run description (context, pinned centroids, residual loads, batches),
 runs the harness and parses what the C ABI returned.
 
@@ -32,6 +34,7 @@ SOURCES = ("salt_plan.hip", "salt_apply.hip", "salt_fuse_gram.hip", "salt_swap.h
 HEADERS = ("salt_device.h", "salt_internal.h", "salt_layout.h", "salt_launch.h")
 PROGRAMS = ("capture", "gram")   # tests/cpu_kernels/<name>.cpp
 DYN_LDS = "extern __shared__ __attribute__((aligned(16))) char lds[];"
+WORK_UNIT = "kWorkUnit = 1e-6;"
 CLANG = "/opt/rocm/llvm/bin/clang++"
 
 
@@ -72,6 +75,9 @@ def _build(exe: str) -> str:
     for n in SOURCES + HEADERS:
         text = open(os.path.join(CSRC, n)).read()
         text = text.replace(DYN_LDS, "char* lds = salt_cpu::g_dyn_lds;")
+        if n == "salt_launch.h":
+            assert WORK_UNIT in text
+            text = text.replace(WORK_UNIT, WORK_UNIT.replace("1e-6", "1e-4"))
         with open(os.path.join(src, n), "w") as f:
             f.write(text)
     mains = [os.path.join(SHIM, n + ".cpp") for n in ("harness",) + PROGRAMS]

@@ -350,6 +350,7 @@ inline int salt_cpu_update_dpp(int, int v, int ctrl, int, int, bool) {
   return salt_cpu::wave_xchg(v, (l & ~3) | ((ctrl >> (2 * (l & 3))) & 3));
 }
 #define __builtin_amdgcn_update_dpp salt_cpu_update_dpp
+#define __builtin_amdgcn_sched_barrier(mask)   // an order hint for the GPU compiler only
 #define __HIP_MEMORY_SCOPE_SYSTEM 0
 #define __hip_atomic_store(p, v, order, scope) __atomic_store_n(p, v, order)
 inline int atomicAdd(int* p, int v) {
