@@ -559,8 +559,8 @@ salt_status build_impl(salt_ctx* ctx, salt_plan* plan, hipStream_t s) {
       plan->deferred = false;
     }
     salt::PlanLaunch pl{};
-    const int4* host = plan->staging_dev + (size_t)plan->stage * plan->stage_len;
-    pl.maps = plan->in_place ? host : (plan->fixed ? plan->staged_cap : plan->staged_dev);
+    pl.maps = plan->fixed ? plan->staged_cap : plan->staged_dev;
+    if (plan->in_place) pl.maps = plan->staging_dev + (size_t)plan->stage * plan->stage_len;
     pl.tiles = plan->staged_dev + plan->T;
     pl.tiles_src = plan->in_place || plan->fixed ? pl.maps + plan->T : nullptr;
     pl.keys = plan->keys;

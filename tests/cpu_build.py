@@ -82,20 +82,22 @@ def _build(exe: str) -> str:
             f.write(text)
     mains = [os.path.join(SHIM, n + ".cpp") for n in ("harness",) + PROGRAMS]
     srcs = [os.path.join(src, n) for n in SOURCES] + mains
+    # (host arithmetic on pointers that are null or leave their buffer is an error too)
     flags = ["-std=c++17", "-O1", "-g", "-fsanitize=address", "-fno-omit-frame-pointer", "-w"]
     for old in os.listdir(BUILD):
         if "-" in old and not old.endswith(os.path.basename(exe).split("-")[1]):
             os.remove(os.path.join(BUILD, old))
     # one compiler process per source, then one link per program (the harness last)
     objs = [os.path.join(src, os.path.basename(s) + ".o") for s in srcs]
-    procs = [subprocess.Popen([CLANG, *flags, f"-I{SHIM}", f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}",
+    checked = {os.path.join(src, "salt_runtime.cpp"): ["-fsanitize=pointer-overflow", "-fno-sanitize-recover=all"]}
+    procs = [subprocess.Popen([CLANG, *flags, *checked.get(s, []), f"-I{SHIM}", f"-I{os.path.join(ROOT, 'include')}", f"-I{CSRC}",
                                "-x", "c++", "-c", s, "-o", o], stdout=subprocess.PIPE, stderr=subprocess.PIPE,
                               text=True) for s, o in zip(srcs, objs)]
     errs = [(p.communicate()[1], p.returncode) for p in procs]
     lib, links = objs[:len(SOURCES)], []
     for n, o in reversed(list(zip(("harness",) + PROGRAMS, objs[len(SOURCES):]))):
         out = exe.replace("harness-", n + "-")
-        links.append(subprocess.run([CLANG, *flags, *lib, o, "-o", out + ".tmp"], capture_output=True, text=True))
+        links.append(subprocess.run([CLANG, *flags, "-fsanitize=pointer-overflow", *lib, o, "-o", out + ".tmp"], capture_output=True, text=True))
         if links[-1].returncode == 0:
             os.replace(out + ".tmp", out)
     if any(rc for _, rc in errs) or any(l.returncode for l in links):
