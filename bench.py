@@ -6,8 +6,9 @@
 Prints ONE JSON line.  A step is one pass of the hot path over one batch: the
 device plan build (grouping by centroid) followed by the apply of every table of
 the workload, a decoder layer's seven tables per salt_apply_batch (one shrink and
-one expand launch per layer).  Inputs (x, y, maps, pinned centroids, resident
-residuals) are in HBM before the timed region starts.
+one expand launch per layer).  Inputs (x, y, pinned centroids, resident residuals)
+are in HBM before the timed region starts, and the maps are staged: in HBM above
+4096 tokens, else in page-locked memory, from which the timed build reads them.
 
 Default workload (the metric's configuration): Llama-3.2-3B, all seven
 projections of its 28 layers (196 tables), bf16 prefill of 8192 tokens in 256
@@ -726,7 +727,7 @@ def main():
                    "centroids": f"{w.n_centroids} x r{w.r_c}", "residual_slots": f"{w.n_slots} x r<={w.r_u_max}",
                    "accumulation": "fp32", "rotation": spec["rot"],
                    "step": "salt_plan_build + one salt_apply_batch per decoder layer (its 7 tables); maps staged "
-                           "in HBM beforehand"},
+                           "beforehand (in HBM above 4096 tokens, else page-locked and read by the build)"},
         "achieved_GBps_step": res["step_GBps"],
         "step_bytes": res["step_bytes"],
         "tiling": res["tiling"],

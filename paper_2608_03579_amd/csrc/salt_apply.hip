@@ -387,8 +387,8 @@ k_shrink(const ApplyLaunch a) {
 }
 
 // Residual ranks above 2 where wide_shrink says so (long-tail concatenated adapters,
-// large batches of plain LoRA ones): the shrink of a 16-token tile whose tokens bring up to kRankChunk rows of A_u each
-// in this block's rank chunk.  Bound by the bandwidth of those rows (every row is
+// large batches of plain LoRA ones): the shrink of a 16-token tile whose tokens
+// bring up to kRankChunk rows of A_u each in this block's rank chunk.  Bound by the bandwidth of those rows (every row is
 // one user's, read once per tile), so the kernel is laid out for rows in flight:
 //  - the tile header carries its group's largest rank: a block of a chunk past
 //    it leaves at once, and a tile of ranks up to G reads one group of rows per

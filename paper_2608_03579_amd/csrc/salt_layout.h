@@ -299,8 +299,7 @@ SALT_HD int expand_col(int col0, int i, int b4) {
 // consecutive vectors of one row: lane l = 16 g + 4 q + b reads in load j (0..3)
 // row 4 q + j, vector 4 g + b.  The memory pipeline takes a wave's 16-byte lanes
 // quad by quad, one 64-byte piece each; in the row layout every lane is a piece
-// of its own, and the address units of the prefill's expand were busy 73 % of
-// the time (45 % in the quad layout, 236 -> 212 us).
+// of its own (prefill T = 8192, rank 1, the expand: 236 -> 212 us).
 // A transpose of 4 registers x 4 lanes inside each quad turns loads j into the
 // operand form: lane l, register s holds row l & 15, vector 4 g + s, that is
 // elements 32 g + 8 s + 0..7.

@@ -177,9 +177,9 @@ __device__ __forceinline__ int count_below(const uint64_t* l, int n, uint64_t k)
 // thread: place tid + NT e.  Each wave sorts runs of 64 keys on its registers;
 // then pairs of runs merge, level by level, a key's place being its place in its
 // run plus the number of keys below it in the other (a binary search in LDS).
-// Bound by latency: one barrier to a level, against one to each of the 36 (T =
-// 1531) steps of a whole bitonic network in LDS, which took 22 us; 17 us
-// here, with the maps read over PCIe (12 us of a copy ahead of it gone as well).
+// Bound by latency: one barrier to a level (5 at T = 1531), against 20 of a bitonic
+// network whose longer steps ran in LDS, which took 22 us; 17 us here, with the
+// maps read over PCIe (12 us of a copy ahead of it gone as well).
 template <int NT, int KPT>
 __global__ void __launch_bounds__(NT) k_plan_sort(const PlanLaunch a) {
   constexpr int NC = NT * KPT;
@@ -250,8 +250,7 @@ __global__ void __launch_bounds__(NT) k_plan_sort(const PlanLaunch a) {
 
 // Up to 64 tokens, in one wave: a key's place is the number of keys below it, so
 // there is nothing to sort.  Bound by latency (a launch and two rounds to
-// memory): the
-// kernel takes 4.6 us against 4.9, and the copy that the sort waited for is gone
+// memory): the kernel takes 4.6 us against 4.9, and the copy that the sort waited for is gone
 // (a decode step of four new tokens, maps to y: 30.9 -> 21.6 us).
 __global__ void __launch_bounds__(64) k_plan_small(const PlanLaunch a, const PlanArgs m) {
   __shared__ uint64_t s_keys[kArgTokens], s_sorted[kArgTokens];

@@ -2,11 +2,12 @@
 two low-rank updates, computed from r x r Gram products of their factors).
 
 Expected values: the oracle forms the dense updates dW = A B in float64.  Bound
-per term: a Gram entry is a sum of K <= 16384 exact products (bf16) taken as 16
-MFMA steps of 32 per 512-chunk and at most 32 fp32 atomic adds across chunks, so
-its error is below (16 + 32) 2^-24 < 2^-18 of sum_k |x_k y_k|; a term (a sum of
-products of two Grams) is then within 2^-17 T_abs, where T_abs is the same term
-from absolute values; the test allows 2^-16 T_abs.  Adapters are built so that a
+per term: a Gram entry is a sum of K <= 16384 exact products (bf16), above rank 32
+taken as 64 MFMA steps of 32 per 2048-chunk and at most 8 fp32 atomic adds across
+chunks (up to rank 32: 8 steps, 3 adds, and chunks added in float64), so its
+error is below 72 2^-24 of sum_k |x_k y_k|; a term (a sum of products of two
+Grams) is then within 144 2^-24 < 2^-16 T_abs, where T_abs is the same term from
+absolute values, which is what the test allows.  Adapters are built so that a
 dropped, transposed or mis-paired Gram moves a term by more than that (the
 second adapter holds the first one's rows, reversed, plus a few of its own).  Integer factors give exact Grams
 (every sum below 2^24) and must match bit for bit.
